@@ -104,7 +104,8 @@ def draw(rng):
         big = rng.random() < 0.5
         return dict(kind=kind, streams=rng.randint(2, 12), wmin=320 if not big else 640,
                     wmax=640 if not big else 2560, hmin=180 if not big else 360,
-                    hmax=360 if not big else 1440, sizes=rng.randrange(1 << 20), half=half)
+                    hmax=360 if not big else 1440, sizes=rng.randrange(1 << 20),
+                    half=half or big)
     if kind == "train":
         w, h = _size(rng, 160, 960)
         return dict(kind=kind, w=w, h=h)
