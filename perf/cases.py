@@ -102,7 +102,7 @@ def draw(rng):
         return dict(kind=kind, w=w, h=h, half=half)
     if kind == "batch":
         big = rng.random() < 0.5
-        return dict(kind=kind, streams=rng.randint(2, 12), wmin=320 if not big else 640,
+        return dict(kind=kind, streams=rng.randint(2, 6 if big else 12), wmin=320 if not big else 640,
                     wmax=640 if not big else 2560, hmin=180 if not big else 360,
                     hmax=360 if not big else 1440, sizes=rng.randrange(1 << 20),
                     half=half or big)
