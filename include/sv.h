@@ -466,7 +466,7 @@ int sv_mlp_forward(const sv_mlp *w, const void *feat, float *alpha, float *kappa
  * (binary32 planes with the pitch of d: dL/dalpha and dL/dkappa per pixel)
  * with respect to every parameter, times `scale`, written to `grad`
  * (SV_MLP_PARAMS binary32, flat order).  The forward pass is recomputed.
- * `work`: device buffer of sv_mlp_backward_work_bytes(d) bytes (per-wave
+ * `work`: device buffer of sv_mlp_backward_work_bytes(d) bytes (per-workgroup
  * partial sums, reduced in a fixed order, so the result is deterministic). */
 int sv_mlp_backward(const sv_mlp *w, const void *feat, const float *d_alpha,
                     const float *d_kappa, float scale, float *grad, void *work,

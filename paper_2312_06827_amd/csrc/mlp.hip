@@ -14,22 +14,13 @@ struct MlpArgs {
     const uint4 *feat;  // 2 x 16 bytes per pixel
     float *alpha, *kappa;
     const float *d_alpha, *d_kappa;
-    float *part;  // backward: per-wave partial gradients
+    float *part;  // backward: per-workgroup partial gradients
     int w, h, pitch;
-    int npix, nblk;  // pixels, 32-pixel blocks
+    int npix, ngrp;  // pixels, 64-pixel groups
 };
 
-__device__ __forceinline__ void load_x(const MlpArgs &a, int p, int hf, bf16x4 (&x)[2]) {
-    // features 8 kb + 4 hf .. + 3 of pixel p: 8 bytes inside its 32-byte row
-    const uint2 *row = (const uint2 *)(a.feat + 2 * (size_t)p);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-        const uint2 v = row[2 * kb + hf];
-        x[kb][0] = (short)(v.x & 0xFFFFu);
-        x[kb][1] = (short)(v.x >> 16);
-        x[kb][2] = (short)(v.y & 0xFFFFu);
-        x[kb][3] = (short)(v.y >> 16);
-    }
+__device__ __forceinline__ bf16x8 load_x(const MlpArgs &a, int p, int hf) {
+    return feature_operand((const uint2 *)(a.feat + 2 * (size_t)p), hf);
 }
 
 __device__ __forceinline__ uint32_t plane_off(const MlpArgs &a, int p) {
@@ -37,22 +28,39 @@ __device__ __forceinline__ uint32_t plane_off(const MlpArgs &a, int p) {
     return (uint32_t)y * (uint32_t)a.pitch + (uint32_t)x;
 }
 
+// A wave takes 64 pixels at a time, as two 32-pixel blocks: block hf's
+// outputs are then kept by the lanes of half hf, so that the heads, the
+// plane addresses and the stores are one pixel per lane. One head
+// evaluation per 64 pixels instead of two, and one-instruction roundings:
+// 43 -> 31 us at 1920x1080 (83 MB: 16 us at the rate of a large copy).
 __global__ __launch_bounds__(256) void mlp_forward_k(MlpArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 31, hf = lane >> 5;
-    FwdW f;
-    load_fwd(a.params, a.wq, col, hf, f);
-    for (int blk = blockIdx.x * 4 + wave; blk < a.nblk; blk += gridDim.x * 4) {
-        const int p = blk * 32 + col;
-        const bool valid = p < a.npix;
-        bf16x4 x[2];
-        load_x(a, valid ? p : a.npix - 1, hf, x);
-        FwdOut r;
-        forward_block(a.params, f, x, hf, r);
-        if (valid && hf == 0) {
+    __shared__ u32x4 s_w[kNetStage];
+    __shared__ __align__(16) float s_b[kNetFloats];
+    NetStage ns;
+    net_issue(a.params, a.wq, ns);
+    net_store(ns, s_w, s_b);
+    __syncthreads();
+    NetW f;
+    load_operands(s_w, lane, f);
+    load_floats(s_b, hf, f);
+    for (int g = blockIdx.x * 4 + wave; g < a.ngrp; g += gridDim.x * 4) {
+        const int p = g * 64 + lane;
+        float o0 = 0.f, o1 = 0.f;
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk) {
+            FwdOut r;
+            forward_block(f, load_x(a, min(g * 64 + blk * 32 + col, a.npix - 1), hf), r);
+            if (blk == hf) {
+                o0 = r.o0;
+                o1 = r.o1;
+            }
+        }
+        if (p < a.npix) {
             const uint32_t o = plane_off(a, p);
             float al, ka;
-            mlp_heads(r.o0, r.o1, al, ka);
+            mlp_heads(o0, o1, al, ka);
             if (a.alpha) a.alpha[o] = al;
             if (a.kappa) a.kappa[o] = ka;
         }
@@ -60,160 +68,177 @@ __global__ __launch_bounds__(256) void mlp_forward_k(MlpArgs a) {
 }
 
 // ---- backward ------------------------------------------------------------
+//
+// The weight gradients are contractions over pixels, so their operands hold
+// pixels along K: lane l gives eight pixels of unit l % 32.  An operand with
+// units along K, taken as A against a unit matrix as B, leaves exactly that
+// in the accumulators (one product by 1 and zeros: exact), so the activations
+// and the back-propagated gradients are turned on the matrix cores instead of
+// through LDS.  Every value that is rounded to bfloat16 is formed as in a
+// plain backward pass; 26 matrix instructions per 32 pixels, no LDS stores
+// and no barrier in the loop.At 1920x1080
+// 99 us against 242 us for the form that turned four 32 x 32 tiles a block
+// through 2-byte LDS stores and rounded in software.  The chain of dependent
+// products at two waves per SIMD (256 registers) bounds it: with both of a
+// wave's blocks in flight it spills, 176 us, and one wave per SIMD hides less.
 
-constexpr int kTP = 36;  // LDS tile row pitch in bfloat16 (32 + 4: fewer bank conflicts)
+// What the backward pass holds beside NetW.
+struct BwdW {
+    bf16x8 w2t[2];   // W2^T as A operand: [h1 unit = lane % 32][h2 unit]
+    bf16x8 unit[2];  // K values 16 j + drow(i, hf) to their own columns
+    bf16x8 unit_g;   // K values 0 and 1 of each half to columns 16 and 17
+};
+
+__device__ __forceinline__ void load_bwd(const uint16_t *wq, int lane, BwdW &b) {
+    const int col = lane & 31, hf = lane >> 5;
+    constexpr uint32_t kOne = 0x3F80u;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        u32x4 p, q;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int u = drow(8 * j + 2 * i, hf);
+            p[i] = wq[kOffW2 + u * SV_MLP_HIDDEN + col] |
+                   ((uint32_t)wq[kOffW2 + (u + 1) * SV_MLP_HIDDEN + col] << 16);
+            q[i] = (col == u ? kOne : 0u) | (col == u + 1 ? kOne << 16 : 0u);
+        }
+        b.w2t[j] = as_operand(p);
+        b.unit[j] = as_operand(q);
+    }
+    b.unit_g = as_operand(u32x4{col == 16 ? kOne : col == 17 ? kOne << 16 : 0u, 0u, 0u, 0u});
+}
+
+// The operand pair (units along K) with its pixels along K instead.
+__device__ __forceinline__ f32x16 turned(const BwdW &w, const bf16x8 (&v)[2]) {
+    f32x16 d = {};
+    d = mfma16(v[0], w.unit[0], d);
+    return mfma16(v[1], w.unit[1], d);
+}
 
 // Sum over the 32 lanes of one half-wave (butterfly, fixed order).
 __device__ __forceinline__ float half_sum(float v) {
-    v += __shfl_xor(v, 1, 64);
-    v += __shfl_xor(v, 2, 64);
-    v += __shfl_xor(v, 4, 64);
-    v += __shfl_xor(v, 8, 64);
-    v += __shfl_xor(v, 16, 64);
+#pragma unroll
+    for (int m = 1; m < 32; m *= 2) v += __shfl_xor(v, m, 64);
     return v;
 }
 
-__device__ __forceinline__ bf16x4 tile_read(const uint16_t *t, int row, int k0) {
-    const uint2 v = *(const uint2 *)(t + row * kTP + k0);
-    bf16x4 r;
-    r[0] = (short)(v.x & 0xFFFFu);
-    r[1] = (short)(v.x >> 16);
-    r[2] = (short)(v.y & 0xFFFFu);
-    r[3] = (short)(v.y >> 16);
-    return r;
-}
+struct BwdAcc {
+    f32x16 dw1, dw2, dw3;  // rows: units (of W1, W2; of W3: h2 units), columns lane % 32
+    f32x16 db1, db2;       // this lane's units and pixels
+    float db3a, db3b;      // this lane's pixels
+};
 
-// Every wave of a workgroup runs the same number of iterations (a wave
-// whose block is past the end works on an empty block), so the workgroup
-// barriers around the LDS transposes are uniform.
-__global__ __launch_bounds__(256) void mlp_backward_k(MlpArgs a) {
-    // per wave: tiles [unit or feature][pixel] of g_h2, h1, g_h1, x
-    __shared__ __align__(16) uint16_t lds[4][4][32 * kTP];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = lane & 31, hf = lane >> 5;
-    uint16_t *t_gh2 = lds[wave][0], *t_h1 = lds[wave][1], *t_gh1 = lds[wave][2],
-             *t_x = lds[wave][3];
-    // rows 16..31 of the x tile stay zero: the feature dimension is padded
-    for (int i = lane; i < 32 * kTP; i += 64) t_x[i] = 0;
-    FwdW f;
-    load_fwd(a.params, a.wq, col, hf, f);
-    bf16x4 w2t[4];  // A operand of W2^T: [h1 unit = col][h2 unit]
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            w2t[kb][i] = (short)a.wq[kOffW2 + (8 * kb + 4 * hf + i) * SV_MLP_HIDDEN + col];
-    f32x16 dw1, dw2;
+// One 32-pixel block: g holds the two head gradients of pixel lane % 32 in
+// bfloat16, in both halves of the wave; `first` in the lower one.
+__device__ __forceinline__ void backward_block(const NetW &f, const BwdW &w, bf16x8 x,
+                                               const FwdOut &r, uint32_t g, bool first,
+                                               BwdAcc &acc) {
+    const float g0 = __uint_as_float(g << 16), g1 = __uint_as_float(g & 0xFFFF0000u);
+    f32x16 gh2;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        dw1[i] = 0.f;
-        dw2[i] = 0.f;
+        gh2[i] = r.a2[i] > 0.f ? fmaf(f.w3a[i], g0, f.w3b[i] * g1) : 0.f;
+        acc.db2[i] += gh2[i];
     }
-    float dw3a[16], dw3b[16], db1[16], db2[16];
+    const bf16x8 gb[2] = {pack_operand(gh2, 0), pack_operand(gh2, 1)};
+    f32x16 gh1 = {};
+    gh1 = mfma8(w.w2t[0], gb[0], gh1);
+    gh1 = mfma8(w.w2t[1], gb[1], gh1);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) dw3a[i] = dw3b[i] = db1[i] = db2[i] = 0.f;
-    float db3a = 0.f, db3b = 0.f;
-    const int stride = gridDim.x * 4;
-    for (int base = blockIdx.x * 4; base < a.nblk; base += stride) {
-        const int blk = base + wave;
+    for (int i = 0; i < 16; ++i) {
+        gh1[i] = r.a1[i] > 0.f ? gh1[i] : 0.f;
+        acc.db1[i] += gh1[i];
+    }
+    const bf16x8 g1b[2] = {pack_operand(gh1, 0), pack_operand(gh1, 1)};
+    // features in columns 0..15, the head gradients in 16 and 17
+    f32x16 xg = {};
+    xg = mfma16(x, w.unit[0], xg);
+    xg = mfma16(as_operand(u32x4{first ? g : 0u, 0u, 0u, 0u}), w.unit_g, xg);
+    const f32x16 g1t = turned(w, g1b), g2t = turned(w, gb), h1t = turned(w, r.h1),
+                 h2t = turned(w, r.h2);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const bf16x8 xgo = pack_operand(xg, j);
+        acc.dw1 = mfma16(pack_operand(g1t, j), xgo, acc.dw1);
+        acc.dw2 = mfma16(pack_operand(g2t, j), pack_operand(h1t, j), acc.dw2);
+        acc.dw3 = mfma16(pack_operand(h2t, j), xgo, acc.dw3);
+    }
+}
+
+__global__ __launch_bounds__(256, 2) void mlp_backward_k(MlpArgs a) {
+    __shared__ float s_part[4][SV_MLP_PARAMS];
+    __shared__ u32x4 s_w[kNetStage];
+    __shared__ __align__(16) float s_b[kNetFloats];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = lane & 31, hf = lane >> 5;
+    NetStage ns;
+    net_issue(a.params, a.wq, ns);
+    net_store(ns, s_w, s_b);
+    BwdW w;
+    load_bwd(a.wq, lane, w);
+    __syncthreads();
+    NetW f;
+    load_operands(s_w, lane, f);
+    BwdAcc acc = {};
+    const int nblk = (a.npix + 31) / 32;
+    for (int blk = blockIdx.x * 4 + wave; blk < nblk; blk += gridDim.x * 4) {
         const int p = blk * 32 + col;
-        const bool valid = blk < a.nblk && p < a.npix;
-        bf16x4 x[2];
-        load_x(a, valid ? p : 0, hf, x);
-        FwdOut r;
-        forward_block(a.params, f, x, hf, r);
-        // gradients of the outputs
+        const bool valid = p < a.npix;
+        const bf16x8 x = load_x(a, valid ? p : 0, hf);
         float da = 0.f, dk = 0.f;
         if (valid) {
             const uint32_t o = plane_off(a, p);
             da = a.d_alpha ? a.d_alpha[o] : 0.f;
             dk = a.d_kappa ? a.d_kappa[o] : 0.f;
         }
+        FwdOut r;
+        // the binary32 parameters are read from LDS where they are used:
+        // held over the loop their registers spill
+        load_floats(s_b + vofs(0u), hf, f);
+        forward_block(f, x, r);
+        const float o0 = r.o0, o1 = r.o1;
         // the heads' slopes without cancellation: sigmoid' = e / (1 + e)^2
         // with e = exp(-|o|), and 1 - tanh^2 = 4 e / (1 + e)^2 with
         // e = exp(-2|o|) (1 - sg and 1 - th^2 would lose every digit once
         // the heads saturate)
-        const float e0 = expf(-fabsf(r.o0)), d0 = 1.0f / (1.0f + e0);
-        const float e1 = expf(-2.0f * fabsf(r.o1)), d1 = 1.0f / (1.0f + e1);
-        const float kap = exp2f(2.0f * tanhf(r.o1));
+        const float e0 = expf(-fabsf(o0)), d0 = 1.0f / (1.0f + e0);
+        const float e1 = expf(-2.0f * fabsf(o1)), d1 = 1.0f / (1.0f + e1);
+        const float kap = exp2f(2.0f * tanhf(o1));
         const float g0 = da * (1.0f - kAlphaMin) * (e0 * d0 * d0);
         const float g1 = dk * kap * 0.69314718055994531f * 2.0f * (4.0f * e1 * d1 * d1);
-        const float g0q = from_bf16(to_bf16(g0)), g1q = from_bf16(to_bf16(g1));
         if (hf == 0) {
-            db3a += g0;
-            db3b += g1;
+            acc.db3a += g0;
+            acc.db3b += g1;
         }
-        // layer 3 and the gradient reaching layer 2
-        float gh2[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            dw3a[i] = fmaf(g0q, r.h2[i], dw3a[i]);
-            dw3b[i] = fmaf(g1q, r.h2[i], dw3b[i]);
-            gh2[i] = r.a2[i] > 0.f ? fmaf(f.w3a[i], g0q, f.w3b[i] * g1q) : 0.f;
-            db2[i] += gh2[i];
-        }
-        bf16x4 gb[4];
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) gb[kb][i] = (short)to_bf16(gh2[4 * kb + i]);
-        // gradient reaching layer 1: W2^T g_h2, masked by a1 > 0
-        f32x16 g1acc;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) g1acc[i] = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) g1acc = mfma(w2t[kb], gb[kb], g1acc);
-        float gh1[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            gh1[i] = r.a1[i] > 0.f ? g1acc[i] : 0.f;
-            db1[i] += gh1[i];
-        }
-        // transposes for the weight gradients (contractions over pixels)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int u = drow(i, hf);
-            t_gh2[u * kTP + col] = (uint16_t)gb[i >> 2][i & 3];
-            t_h1[u * kTP + col] = (uint16_t)r.h1[i >> 2][i & 3];
-            t_gh1[u * kTP + col] = to_bf16(gh1[i]);
-        }
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) t_x[(8 * kb + 4 * hf + i) * kTP + col] = (uint16_t)x[kb][i];
-        __syncthreads();
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            const int k0 = 8 * kb + 4 * hf;
-            dw2 = mfma(tile_read(t_gh2, col, k0), tile_read(t_h1, col, k0), dw2);
-            dw1 = mfma(tile_read(t_gh1, col, k0), tile_read(t_x, col, k0), dw1);
-        }
-        __syncthreads();
+        backward_block(f, w, x, r, pack_bf16(g0, g1), hf == 0, acc);
     }
-    // this wave's partial gradient, flat order
-    float *out = a.part + (size_t)(blockIdx.x * 4 + wave) * SV_MLP_PARAMS;
+    // this workgroup's partial gradient, flat order: the four waves' sums
+    // joined in LDS
+    float *sp = s_part[wave];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int u = drow(i, hf);
-        out[kOffW2 + u * SV_MLP_HIDDEN + col] = dw2[i];
-        if (col < SV_MLP_IN) out[kOffW1 + u * SV_MLP_IN + col] = dw1[i];
-        const float s3a = half_sum(dw3a[i]), s3b = half_sum(dw3b[i]);
-        const float s1 = half_sum(db1[i]), s2 = half_sum(db2[i]);
+        sp[kOffW2 + u * SV_MLP_HIDDEN + col] = acc.dw2[i];
+        if (col < SV_MLP_IN) sp[kOffW1 + u * SV_MLP_IN + col] = acc.dw1[i];
+        if (col == 16) sp[kOffW3 + u] = acc.dw3[i];
+        if (col == 17) sp[kOffW3 + SV_MLP_HIDDEN + u] = acc.dw3[i];
+        const float s1 = half_sum(acc.db1[i]), s2 = half_sum(acc.db2[i]);
         if (col == 0) {
-            out[kOffW3 + u] = s3a;
-            out[kOffW3 + SV_MLP_HIDDEN + u] = s3b;
-            out[kOffB1 + u] = s1;
-            out[kOffB2 + u] = s2;
+            sp[kOffB1 + u] = s1;
+            sp[kOffB2 + u] = s2;
         }
     }
-    db3a = half_sum(db3a);
-    db3b = half_sum(db3b);
-    db3a += __shfl_xor(db3a, 32, 64);
-    db3b += __shfl_xor(db3b, 32, 64);
+    float s3a = half_sum(acc.db3a), s3b = half_sum(acc.db3b);
+    s3a += __shfl_xor(s3a, 32, 64);
+    s3b += __shfl_xor(s3b, 32, 64);
     if (lane == 0) {
-        out[kOffB3] = db3a;
-        out[kOffB3 + 1] = db3b;
+        sp[kOffB3] = s3a;
+        sp[kOffB3 + 1] = s3b;
     }
+    __syncthreads();
+    float *out = a.part + (size_t)blockIdx.x * SV_MLP_PARAMS;
+    for (int j = threadIdx.x; j < SV_MLP_PARAMS; j += 256)
+        out[j] = (s_part[0][j] + s_part[1][j]) + (s_part[2][j] + s_part[3][j]);
 }
 
 // Sum of the nw partial gradients, one parameter per column.  A workgroup
@@ -221,7 +246,7 @@ __global__ __launch_bounds__(256) void mlp_backward_k(MlpArgs a) {
 // over 64 groups of lanes, whose sums a tree in LDS joins in a fixed order.
 // One thread per parameter walking all rows put the whole sum, up to 8192
 // dependent loads, on seven workgroups: latency alone, 1910 us at 1920x1080
-// and 420 us at 320x180 against 24 and 7 us now.  Shorter chains also
+// and 420 us at 320x180 against 5 and 4 us now (of 2048 and 900 partials: 24 and 7 of 8192 and 1800).  Shorter chains also
 // round less.
 constexpr int kRedCols = 16, kRedRows = 64;
 
@@ -399,9 +424,15 @@ __global__ __launch_bounds__(256) void kappa_grad_k(KappaGradArgs a) {
     a.d_kappa[o] += (float)(g * (2.0 / 3.0));
 }
 
-inline unsigned mlp_grid(int nblk) {
-    const int wgs = (nblk + 3) / 4;
-    return (unsigned)std::max(1, std::min(wgs, 256 * 8));
+// Workgroups of a network kernel over ngrp 64-pixel groups: one group per
+// wave while that fits `per_cu` workgroups on each CU, then as many groups
+// per wave as it takes.  The backward pass keeps its weights and its
+// sums in registers, two waves per SIMD; more workgroups than are
+// resident would only repeat its loads of the weights and its final sums.
+constexpr int kFwdPerCU = 8, kBwdPerCU = 2;
+
+inline unsigned mlp_grid(int ngrp, int per_cu) {
+    return (unsigned)std::max(1, std::min((ngrp + 3) / 4, 256 * per_cu));
 }
 
 inline bool valid_mlp(const sv_mlp *w) { return w && w->params && w->wq; }
@@ -430,16 +461,15 @@ extern "C" int sv_mlp_forward(const sv_mlp *w, const void *feat, float *alpha, f
     a.h = d.h;
     a.pitch = d.pitch;
     a.npix = d.w * d.h;
-    a.nblk = (a.npix + 31) / 32;
-    hipLaunchKernelGGL(mlp_forward_k, dim3(mlp_grid(a.nblk)), dim3(256), 0, as_stream(stream), a);
+    a.ngrp = (a.npix + 63) / 64;
+    hipLaunchKernelGGL(mlp_forward_k, dim3(mlp_grid(a.ngrp, kFwdPerCU)), dim3(256), 0, as_stream(stream), a);
     return hip_status(hipGetLastError());
 }
 
 extern "C" size_t sv_mlp_backward_work_bytes(sv_dims d) {
     using namespace sv;
     if (check_dims(d) < 0) return 0;
-    const int nblk = (d.w * d.h + 31) / 32;
-    return (size_t)mlp_grid(nblk) * 4u * SV_MLP_PARAMS * sizeof(float);
+    return (size_t)mlp_grid((d.w * d.h + 63) / 64, kBwdPerCU) * SV_MLP_PARAMS * sizeof(float);
 }
 
 extern "C" int sv_mlp_backward(const sv_mlp *w, const void *feat, const float *d_alpha,
@@ -464,7 +494,7 @@ extern "C" int sv_mlp_backward(const sv_mlp *w, const void *feat, const float *d
     a.h = d.h;
     a.pitch = d.pitch;
     a.npix = d.w * d.h;
-    a.nblk = (a.npix + 31) / 32;
+    a.ngrp = (a.npix + 63) / 64;
     const span ws{(uintptr_t)work, (uintptr_t)work + sv_mlp_backward_work_bytes(d)};
     const span gs{(uintptr_t)grad, (uintptr_t)grad + SV_MLP_PARAMS * sizeof(float)};
     const span fs{(uintptr_t)feat, (uintptr_t)feat + (size_t)d.w * (size_t)d.h * 32u};
@@ -472,10 +502,10 @@ extern "C" int sv_mlp_backward(const sv_mlp *w, const void *feat, const float *d
         (d_alpha && (overlaps(ws, plane_span(d_alpha, d, 4)) || overlaps(gs, plane_span(d_alpha, d, 4)))) ||
         (d_kappa && (overlaps(ws, plane_span(d_kappa, d, 4)) || overlaps(gs, plane_span(d_kappa, d, 4)))))
         return SV_EALIAS;
-    const unsigned grid = mlp_grid(a.nblk);
+    const unsigned grid = mlp_grid(a.ngrp, kBwdPerCU);
     hipStream_t s = as_stream(stream);
     hipLaunchKernelGGL(mlp_backward_k, dim3(grid), dim3(256), 0, s, a);
-    launch_reduce((const float *)work, (int)grid * 4, scale, grad, s);
+    launch_reduce((const float *)work, (int)grid, scale, grad, s);
     return hip_status(hipGetLastError());
 }
 

@@ -1,21 +1,32 @@
 // The per-pixel network's forward pass on the matrix cores, shared by the
 // network kernels and by the temporal kernel's learned mode.
 //
-// Matrix layout.  Each layer is computed transposed, Y^T = W X^T, with
-// v_mfma_f32_32x32x8_bf16: A = the weights (32 output units x 8 inputs per
-// instruction), B = 32 pixels x 8 inputs.  Lane l supplies A[l % 32][4 (l/32)
-// + 0..3] and B[4 (l/32) + 0..3][l % 32] of each 8-wide K block and receives
-// D[8 (r/4) + 4 (l/32) + r % 4][l % 32] in accumulator r = 0..15.  So after a
-// layer, accumulators 4 kb .. 4 kb + 3 of a lane are exactly that lane's B
-// operand for K block kb of the next layer: activations never leave
-// registers in the forward pass.
+// Matrix layout.  Each layer is computed transposed, Y^T = W X^T: A = the
+// weights (32 output units x K inputs), B = K inputs x 32 pixels.  An operand
+// is eight bfloat16 values of row l % 32 of A (column l % 32 of B) in lane l,
+// for the K values 16 j + drow(0 .. 7, l / 32): the two operands of two
+// v_mfma_f32_32x32x8_bf16 (K blocks of eight in order), or of one
+// v_mfma_f32_32x32x16_bf16, whose halves may hold any K values as long as
+// A's and B's agree.  The result D[8 (r/4) + 4 (l/32) + r % 4][l % 32] is in
+// accumulator r = 0..15, so after a layer, accumulators 8 j .. 8 j + 7 of a
+// lane, rounded in pairs, are that lane's operand j of the next layer:
+// activations never leave registers in the forward pass. 
+//
+// Which instruction: both round a 32-term sum alike (1.07e-8 rms of the
+// summed magnitudes), but not to the same bits, and a pre-activation that
+// moves by an ulp can round to another bfloat16 value.  The sums that are
+// rounded to bfloat16 next stay with K blocks of eight; sums that are not,
+// and exact ones, take the wider instruction, at half the issue time.
 #pragma once
 #include "sv_internal.h"
 
 namespace sv {
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kOffW1 = 0, kOffB1 = 448, kOffW2 = 480, kOffB2 = 1504, kOffW3 = 1536,
               kOffB3 = 1600;
@@ -28,78 +39,124 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
     return (uint16_t)(u >> 16);
 }
 
-__device__ __forceinline__ float from_bf16(uint16_t h) {
-    return __uint_as_float((uint32_t)h << 16);
+// Two values rounded to bfloat16 (nearest even), a in the low half: one
+// v_cvt_pk_bf16_f32, where to_bf16 takes four instructions a value.
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    f32x2 v;
+    v.x = a;
+    v.y = b;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-__device__ __forceinline__ f32x16 mfma(bf16x4 a, bf16x4 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, c, 0, 0, 0);
+__device__ __forceinline__ bf16x8 as_operand(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+// Accumulators 8 j .. 8 j + 7 as one operand.
+__device__ __forceinline__ bf16x8 pack_operand(const f32x16 &v, int j) {
+    u32x4 p;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = pack_bf16(v[8 * j + 2 * i], v[8 * j + 2 * i + 1]);
+    return as_operand(p);
+}
+
+__device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// The same product as two K blocks of eight, in order.
+typedef short bf16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x16 mfma8(bf16x8 a, bf16x8 b, f32x16 c) {
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const s16x8 p = __builtin_bit_cast(s16x8, a), q = __builtin_bit_cast(s16x8, b);
+    c = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(p.lo, q.lo, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(p.hi, q.hi, c, 0, 0, 0);
 }
 
 // Output unit (row of D) held in accumulator r by a lane of half `hf`.
 __device__ __forceinline__ int drow(int r, int hf) { return 8 * (r >> 2) + 4 * hf + (r & 3); }
 
-// Weights one lane holds for the forward pass.
-struct FwdW {
-    bf16x4 w1[2], w2[4];
-    float w3a[16], w3b[16];  // W3 rows 0 and 1 at this lane's units (bf16 values)
+// ---- the forward pass's weight operands -------------------------------------
+//
+// Three operands of eight values per lane: W1 (unit `lane % 32`; features 14
+// and 15 zero) and W2 (two).  The two-unit output layer runs on the vector
+// units, sixteen terms per lane: its weights are held as binary32.
+constexpr int kNetOps = 3, kOpW1 = 0, kOpW2 = 1;
+
+// Where in the bfloat16 parameters element i of operand k comes from for
+// this lane; -1: zero.
+__device__ __forceinline__ int op_source(int k, int lane, int i) {
+    const int col = lane & 31, hf = lane >> 5;
+    if (k == kOpW1) {
+        const int f = drow(i, hf);
+        return f < SV_MLP_IN ? kOffW1 + col * SV_MLP_IN + f : -1;
+    }
+    return kOffW2 + col * SV_MLP_HIDDEN + drow(8 * (k - kOpW2) + i, hf);
+}
+
+__device__ __forceinline__ uint16_t op_element(const uint16_t *wq, int k, int lane, int i) {
+    const int src = op_source(k, lane, i);
+    const uint16_t v = wq[max(src, 0)];  // always in the array
+    return src < 0 ? (uint16_t)0 : v;
+}
+
+// What one lane holds for the forward pass.
+struct NetW {
+    bf16x8 w1, w2[2];
+    f32x16 b1, b2;    // biases at this lane's D rows
+    f32x16 w3a, w3b;  // W3 rows 0 and 1 there (bfloat16 values)
     float b3a, b3b;
 };
 
-__device__ __forceinline__ void load_fwd(const float *params, const uint16_t *wq, int col, int hf,
-                                         FwdW &f) {
+__device__ __forceinline__ bf16x8 op_load(const uint16_t *wq, int k, int lane) {
+    u32x4 p;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 8 * kb + 4 * hf + i;
-            f.w1[kb][i] = (short)(k < SV_MLP_IN ? wq[kOffW1 + col * SV_MLP_IN + k] : 0);
-        }
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            f.w2[kb][i] = (short)wq[kOffW2 + col * SV_MLP_HIDDEN + 8 * kb + 4 * hf + i];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        f.w3a[r] = from_bf16(wq[kOffW3 + drow(r, hf)]);
-        f.w3b[r] = from_bf16(wq[kOffW3 + SV_MLP_HIDDEN + drow(r, hf)]);
-    }
-    f.b3a = params[kOffB3];
-    f.b3b = params[kOffB3 + 1];
+    for (int i = 0; i < 4; ++i)
+        p[i] = op_element(wq, k, lane, 2 * i) | ((uint32_t)op_element(wq, k, lane, 2 * i + 1) << 16);
+    return as_operand(p);
 }
 
-// Forward pass of one 32-pixel block.  x: this lane's B operands of layer
-// 1; returns the layer-1 and layer-2 pre-activations (with biases), the
-// bfloat16 layer-2 activations as floats, and the two outputs (the same in
-// both halves of the wave).
+// The feature operand of one lane: features 4 hf .. 4 hf + 3 and 8 + 4 hf ..
+// of a 32-byte feature row.
+__device__ __forceinline__ bf16x8 feature_operand(const uint2 *row, int hf) {
+    const uint2 a = row[hf], b = row[2 + hf];
+    return as_operand(u32x4{a.x, a.y, b.x, b.y});
+}
+
+// Forward pass of one 32-pixel block.  x: this lane's operand of layer 1;
+// returns the pre-activations (with biases), the activations as operands, and the two outputs of pixel lane % 32 (the same in both halves).
 struct FwdOut {
     f32x16 a1, a2;
-    bf16x4 h1[4];
-    float h2[16];
+    bf16x8 h1[2], h2[2];
     float o0, o1;
 };
 
-__device__ __forceinline__ void forward_block(const float *params, const FwdW &f,
-                                              const bf16x4 (&x)[2], int hf, FwdOut &r) {
+// max(a, 0), NaN to 0, as one median: fmaxf costs a second instruction that
+// quiets its argument.
+__device__ __forceinline__ f32x16 relu(const f32x16 &a) {
+    f32x16 r;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) r.a1[i] = params[kOffB1 + drow(i, hf)];
-    r.a1 = mfma(f.w1[0], x[0], r.a1);
-    r.a1 = mfma(f.w1[1], x[1], r.a1);
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r.h1[kb][i] = (short)to_bf16(fmaxf(r.a1[4 * kb + i], 0.f));
-#pragma unroll
-    for (int i = 0; i < 16; ++i) r.a2[i] = params[kOffB2 + drow(i, hf)];
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) r.a2 = mfma(f.w2[kb], r.h1[kb], r.a2);
+    for (int i = 0; i < 16; ++i) r[i] = __builtin_amdgcn_fmed3f(a[i], 0.f, INFINITY);
+    return r;
+}
+
+__device__ __forceinline__ void forward_block(const NetW &f, bf16x8 x, FwdOut &r) {
+    r.a1 = mfma8(f.w1, x, f.b1);
+    const f32x16 p1 = relu(r.a1);
+    r.h1[0] = pack_operand(p1, 0);
+    r.h1[1] = pack_operand(p1, 1);
+    r.a2 = mfma8(f.w2[0], r.h1[0], f.b2);
+    r.a2 = mfma8(f.w2[1], r.h1[1], r.a2);
+    const f32x16 p2 = relu(r.a2);
+    r.h2[0] = pack_operand(p2, 0);
+    r.h2[1] = pack_operand(p2, 1);
     float o0 = 0.f, o1 = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        r.h2[i] = from_bf16(to_bf16(fmaxf(r.a2[i], 0.f)));
-        o0 = fmaf(f.w3a[i], r.h2[i], o0);
-        o1 = fmaf(f.w3b[i], r.h2[i], o1);
+    for (int i = 0; i < 16; i += 2) {
+        const uint32_t h = __builtin_bit_cast(u32x4, r.h2[i >> 3])[(i & 7) >> 1];
+        const float lo = __uint_as_float(h << 16), hi = __uint_as_float(h & 0xFFFF0000u);
+        o0 = fmaf(f.w3a[i], lo, o0);
+        o1 = fmaf(f.w3b[i], lo, o1);
+        o0 = fmaf(f.w3a[i + 1], hi, o0);
+        o1 = fmaf(f.w3b[i + 1], hi, o1);
     }
     o0 += __shfl_xor(o0, 32, 64);
     o1 += __shfl_xor(o1, 32, 64);
@@ -107,86 +164,64 @@ __device__ __forceinline__ void forward_block(const float *params, const FwdW &f
     r.o1 = o1 + f.b3b;
 }
 
+// The parameters one workgroup stages in LDS: the operands in lane order (an
+// operand is then one 16-byte read per lane) and, as binary32, the biases of
+// the hidden layers, the rows of W3 and the output biases.
+constexpr int kNetB1 = 0, kNetB2 = SV_MLP_HIDDEN, kNetW3 = 2 * SV_MLP_HIDDEN,
+              kNetB3 = 4 * SV_MLP_HIDDEN, kNetFloats = kNetB3 + 2;
+constexpr int kNetStage = kNetOps * 64;  // 16-byte operand pieces
+static_assert(kNetFloats <= 256, "one float per thread");
 
-// The parameters one workgroup stages in LDS for forward_block_lds: every
-// bfloat16 copy (wq) and the three float bias vectors, packed as B1 | B2 | B3.
-constexpr int kNetBiases = 2 * SV_MLP_HIDDEN + 2;
-constexpr int kNetB1 = 0, kNetB2 = SV_MLP_HIDDEN, kNetB3 = 2 * SV_MLP_HIDDEN;
-constexpr int kNetStageIt = (SV_MLP_PARAMS + 255) / 256;  // bf16 values per thread
+// Entry t of the packed floats.
+__device__ __forceinline__ float net_float(const float *params, const uint16_t *wq, int t) {
+    if (t >= kNetW3 && t < kNetB3)
+        return __uint_as_float((uint32_t)wq[kOffW3 + t - kNetW3] << 16);
+    return params[t < kNetB2   ? kOffB1 + t
+                  : t < kNetW3 ? kOffB2 + t - kNetB2
+                               : kOffB3 + t - kNetB3];
+}
 
 struct NetStage {  // one thread's share of the staging loads
-    uint16_t w[kNetStageIt];
+    uint32_t w[kNetOps];
     float b;
 };
 
 // Issue this thread's staging loads (256 threads cover every value).
 __device__ __forceinline__ void net_issue(const float *params, const uint16_t *wq, NetStage &ns) {
-    // indices clamped into the arrays, so no load can leave them
     const int t = threadIdx.x;
 #pragma unroll
-    for (int k = 0; k < kNetStageIt; ++k)
-        ns.w[k] = wq[min(t + 256 * k, SV_MLP_PARAMS - 1)];
-    const int tb = min(t, kNetBiases - 1);
-    const int bi = tb < SV_MLP_HIDDEN ? kOffB1 + tb
-                   : tb < 2 * SV_MLP_HIDDEN ? kOffB2 + tb - SV_MLP_HIDDEN
-                                            : kOffB3 + tb - 2 * SV_MLP_HIDDEN;
-    ns.b = params[bi];
+    for (int k = 0; k < kNetOps; ++k) {
+        // dword t of operand k: lane t / 4, elements 2 (t % 4) and the next
+        const int lane = t >> 2, i = 2 * (t & 3);
+        ns.w[k] = op_element(wq, k, lane, i) | ((uint32_t)op_element(wq, k, lane, i + 1) << 16);
+    }
+    ns.b = net_float(params, wq, min(t, kNetFloats - 1));
 }
 
-// Store them (each index once; the clamped duplicates are not stored);
-// visible after the caller's next barrier.
-__device__ __forceinline__ void net_store(const NetStage &ns, uint16_t *s_w, float *s_b) {
+// Store them; visible after the caller's next barrier.
+__device__ __forceinline__ void net_store(const NetStage &ns, u32x4 *s_w, float *s_b) {
     const int t = threadIdx.x;
 #pragma unroll
-    for (int k = 0; k < kNetStageIt; ++k) {
-        const int i = t + 256 * k;
-        if (i < SV_MLP_PARAMS) s_w[i] = ns.w[k];
-    }
-    if (t < kNetBiases) s_b[t] = ns.b;
+    for (int k = 0; k < kNetOps; ++k) ((uint32_t *)s_w)[k * 256 + t] = ns.w[k];
+    if (t < kNetFloats) s_b[t] = ns.b;
 }
 
-// forward_block with every parameter read from the workgroup's LDS copy
-// (s_w: the bfloat16 values, s_b: the biases) where it is used: the same
-// operands, operations and order, so bitwise the same outputs, with no
-// weight held in registers across blocks.
-__device__ __forceinline__ void forward_block_lds(const uint16_t *s_w, const float *s_b, int col,
-                                                  int hf, const bf16x4 (&x)[2], FwdOut &r) {
-    bf16x4 w1[2], w2[4];
+__device__ __forceinline__ void load_operands(const u32x4 *s_w, int lane, NetW &f) {
+    f.w1 = as_operand(s_w[kOpW1 * 64 + lane]);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int j = 0; j < 2; ++j) f.w2[j] = as_operand(s_w[(kOpW2 + j) * 64 + lane]);
+}
+
+__device__ __forceinline__ void load_floats(const float *s_b, int hf, NetW &f) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 8 * kb + 4 * hf + i;
-            w1[kb][i] = (short)(k < SV_MLP_IN ? s_w[kOffW1 + col * SV_MLP_IN + k] : 0);
-        }
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            w2[kb][i] = (short)s_w[kOffW2 + col * SV_MLP_HIDDEN + 8 * kb + 4 * hf + i];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) r.a1[i] = s_b[kNetB1 + drow(i, hf)];
-    r.a1 = mfma(w1[0], x[0], r.a1);
-    r.a1 = mfma(w1[1], x[1], r.a1);
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r.h1[kb][i] = (short)to_bf16(fmaxf(r.a1[4 * kb + i], 0.f));
-#pragma unroll
-    for (int i = 0; i < 16; ++i) r.a2[i] = s_b[kNetB2 + drow(i, hf)];
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) r.a2 = mfma(w2[kb], r.h1[kb], r.a2);
-    float o0 = 0.f, o1 = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        r.h2[i] = from_bf16(to_bf16(fmaxf(r.a2[i], 0.f)));
-        o0 = fmaf(from_bf16(s_w[kOffW3 + drow(i, hf)]), r.h2[i], o0);
-        o1 = fmaf(from_bf16(s_w[kOffW3 + SV_MLP_HIDDEN + drow(i, hf)]), r.h2[i], o1);
+    for (int r = 0; r < 16; ++r) {
+        f.b1[r] = s_b[kNetB1 + drow(r, hf)];
+        f.b2[r] = s_b[kNetB2 + drow(r, hf)];
+        f.w3a[r] = s_b[kNetW3 + drow(r, hf)];
+        f.w3b[r] = s_b[kNetW3 + SV_MLP_HIDDEN + drow(r, hf)];
     }
-    o0 += __shfl_xor(o0, 32, 64);
-    o1 += __shfl_xor(o1, 32, 64);
-    r.o0 = o0 + s_b[kNetB3];
-    r.o1 = o1 + s_b[kNetB3 + 1];
+    f.b3a = s_b[kNetB3];
+    f.b3b = s_b[kNetB3 + 1];
 }
 
 // alpha = 0.05 + 0.95 sigmoid(o0), kappa = 2^(2 tanh(o1)).

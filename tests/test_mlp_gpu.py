@@ -128,6 +128,32 @@ def test_backward_parity(N):
     assert torch.equal(grad, g2)
 
 
+@pytest.mark.parametrize("reps,N", [(1, 64), (3, 257), (700, 257)])
+def test_backward_of_repeated_pixels(reps, N):
+    """The gradient of a pixel set repeated: one wave's single group, groups
+    ragged against the repetition, and more groups than resident waves (so
+    the loop over groups, the join of the waves and the split sum of the
+    partials all run) against `reps` times the oracle's gradient."""
+    w = _weights(50 + N)
+    r = np.random.default_rng(N)
+    xs = M.bf16(r.normal(0, 1.2, (14, N)))
+    da, dk = r.normal(0, 1.0, N), r.normal(0, 1.0, N)
+    tile = lambda t: np.tile(t, (reps, 1))
+    like = torch.empty((reps, N), device="cuda")
+    grad = torch.empty(L.SV_MLP_PARAMS, device="cuda")
+    say(f"mlp backward {reps} x {N}")
+    L.sv_mlp_backward(_device_mlp(w), _rows(np.tile(xs, (1, reps))), dev(tile(da)),
+                      dev(tile(dk)), grad, L.mlp_workspace(like), like, scale=1.0 / reps)
+    fw = M.forward(w, xs, bf16_ops=True)
+    ref = M.backward(w, fw, M.head_grads(fw, M.f32(da), M.f32(dk)), bf16_ops=True)
+    _, _, bg, asum, _, _ = B.flip_bounds(w, xs, M.f32(da), M.f32(dk))
+    # binary32 sums of at most about 100 terms in a row (groups of a wave,
+    # rows of the partials, the trees): 2^-16 of the magnitudes, as above
+    err = np.abs(host(grad) - ref)
+    allow = bg + 2.0 ** -16 * asum
+    assert np.all(err <= allow), (int(np.argmax(err - allow)), float((err - allow).max()))
+
+
 def test_adam_parity():
     r = np.random.default_rng(3)
     p0 = M.f32(r.normal(0, 1, L.SV_MLP_PARAMS))
