@@ -298,6 +298,45 @@ def test_variance(H, W):
         assert rel_err(host(out), ref) <= TOL32
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("H,W,radius", [(4, 64, 3), (9, 131, 3), (37, 200, 0), (37, 200, 2),
+                                        (37, 200, 7), (130, 900, 3)])
+def test_variance_dense_tiles_equal_the_list(H, W, radius, dtype):
+    """A pixel's spatial estimate is bitwise the same whether its tile is
+    dense (every pixel short) or lists it (64 short pixels in a 64x4 tile,
+    and one fewer or more around the line between the two forms), and the
+    dense form is the oracle's."""
+    r = np.random.default_rng(700 + H + radius)
+    z, dzdx, dzdy, n = random_gbuf(r, H, W)
+    z[r.random((H, W)) < 0.05] = 0.0
+    q = lambda a: a.astype(np.float16).astype(np.float32) if dtype == torch.float16 else a
+    z, dzdx, dzdy, n = q(z), q(dzdx), q(dzdy), q(n)
+    m1 = r.uniform(0.1, 1.0, (H, W)).astype(np.float32)
+    m2c = (m1 * m1 * r.uniform(0.0, 1.0, (H, W))).astype(np.float32)
+    P = W + 3
+    g = L.GBuf(dev(z, P, dtype), dev(dzdx, P, dtype), dev(dzdy, P, dtype), dev(n, P, dtype))
+    work = L.variance_workspace(empty_like_dev((H, W)))
+
+    def run(hn):
+        out = empty_like_dev((H, W), P)
+        L.sv_variance(dev(m1, P), dev(m2c, P), dev(hn, P, torch.uint8), g, out,
+                      L.VarianceParams(radius=radius), work)
+        assert list_consumed(work)
+        return host(out)
+
+    say(f"variance dense {H}x{W} radius {radius}")
+    short = np.full((H, W), 1, np.uint8)
+    full = run(short)
+    ref = O.variance(m1, m2c.astype(np.float64) + m1.astype(np.float64) ** 2, short, z, dzdx, dzdy,
+                     n, radius=radius)
+    assert rel_err(full, ref) <= TOL32
+    lx = np.arange(W)[None, :] % 64 + 64 * (np.arange(H)[:, None] % 4)  # index in the tile
+    for count in (1, 63, 64, 65, 66):
+        pick = (lx * 37) % 256 < count
+        got = run(np.where(pick, short, 12))
+        np.testing.assert_array_equal(got[pick], full[pick], err_msg=str(count))
+
+
 def test_variance_workspace_across_sizes():
     """One workspace, sized for the largest frame, serves calls of any
     smaller size in any order: the list of one call never leaks into the
