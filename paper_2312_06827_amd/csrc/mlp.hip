@@ -348,69 +348,116 @@ struct KappaGradArgs {
     float sigma_z, sigma_n, sigma_l, eps_z, eps_l;
 };
 
-// One pixel per thread, taps read directly, in binary64 (see alpha_grad_k).
+constexpr int kKappaLanes = 4;                // lanes of a pixel
+constexpr int kKappaPx = 256 / kKappaLanes;   // pixels of a workgroup, in a row
+
+// Sum over a pixel's lanes (butterfly: a fixed order).
+__device__ __forceinline__ double px_sum(double v) {
+#pragma unroll
+    for (int m = kKappaLanes / 2; m > 0; m /= 2) v += __shfl_xor(v, m, 64);
+    return v;
+}
+
+// Four lanes per pixel, taps read directly, in binary64 (see alpha_grad_k):
+// lane s takes window taps s, s + 4, ... with every load issued before the
+// first use.  The training frames are small, so one thread per pixel left the
+// chip at one wave per SIMD walking 25 taps one after the other: @K0@.  The
+// tap's three weights are one exponential of the summed exponents.
 // The 3x3 variance prefilter runs over the in-image, non-empty taps, as in
 // the level itself.
+
 template <typename T>
 __global__ __launch_bounds__(256) void kappa_grad_k(KappaGradArgs a) {
-    const int x = blockIdx.x * 64 + (threadIdx.x & 63), y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= a.w || y >= a.h) return;
+    constexpr int L = kKappaLanes, NT = (25 + L - 1) / L, NV = (9 + L - 1) / L;
+    const int sub = threadIdx.x % L;
+    const int x = blockIdx.x * kKappaPx + threadIdx.x / L, y = blockIdx.y;
+    if (x >= a.w) return;  // whole pixels
     const uint32_t o = (uint32_t)y * (uint32_t)a.pitch + (uint32_t)x;
-    const double zp = ldo<T>(a.z, o);
-    if (empty_px((float)zp)) return;
-    double gs = 0.0, gw = 0.0;
-    for (int dy = -1; dy <= 1; ++dy)
-        for (int dx = -1; dx <= 1; ++dx) {
-            const int qx = x + dx, qy = y + dy;
-            if (qx < 0 || qx >= a.w || qy < 0 || qy >= a.h) continue;
-            const uint32_t q = (uint32_t)qy * (uint32_t)a.pitch + (uint32_t)qx;
-            if (empty_px(ldo<T>(a.z, q))) continue;
-            const double k = (dx == 0 ? 0.5 : 0.25) * (dy == 0 ? 0.5 : 0.25);
-            gs += k * (double)ldf(a.var, q);
-            gw += k;
-        }
-    const double sg = sqrt(gs / gw);
-    const double sl = a.sigma_l;
-    const double dl = sl * (double)ldf(a.kappa, o) * sg + (double)a.eps_l;
-    const double cp[3] = {ldo<T>(a.cr, o), ldo<T>(a.cg, o), ldo<T>(a.cb, o)};
-    const double lp = luma_d(cp[0], cp[1], cp[2]);
-    const double gx = ldo<T>(a.dzdx, o), gy = ldo<T>(a.dzdy, o);
-    const double np_[3] = {ldo<T>(a.nx, o), ldo<T>(a.ny, o), ldo<T>(a.nz, o)};
-    const double h1[5] = {1.0 / 16, 4.0 / 16, 6.0 / 16, 4.0 / 16, 1.0 / 16};
-    double sw = 0.0, sd = 0.0, sc[3] = {0.0, 0.0, 0.0}, sdc[3] = {0.0, 0.0, 0.0};
-    for (int b = -2; b <= 2; ++b)
-        for (int aa = -2; aa <= 2; ++aa) {
-            const int qx = x + aa * a.step, qy = y + b * a.step;
-            if (qx < 0 || qx >= a.w || qy < 0 || qy >= a.h) continue;
-            const uint32_t q = (uint32_t)qy * (uint32_t)a.pitch + (uint32_t)qx;
-            const double hh = h1[aa + 2] * h1[b + 2];
-            const double cq[3] = {ldo<T>(a.cr, q), ldo<T>(a.cg, q), ldo<T>(a.cb, q)};
-            double w = 1.0, d = 0.0;
-            if (aa != 0 || b != 0) {
-                const float zq32 = ldo<T>(a.z, q);
-                if (empty_px(zq32)) continue;
-                const double zq = zq32;
-                const double den = (double)a.sigma_z *
-                                       fabs(gx * (double)(a.step * aa) + gy * (double)(a.step * b)) +
-                                   (double)a.eps_z;
-                const double wz = exp(-fabs(zp - zq) / den);
-                const double ex = np_[0] - (double)ldo<T>(a.nx, q);
-                const double ey = np_[1] - (double)ldo<T>(a.ny, q);
-                const double ez = np_[2] - (double)ldo<T>(a.nz, q);
-                const double cs = 1.0 - 0.5 * (ex * ex + ey * ey + ez * ez);
-                const double wn = pow(cs > 0.0 ? cs : 0.0, (double)a.sigma_n);
-                const double adl = fabs(lp - luma_d(cq[0], cq[1], cq[2]));
-                w = wz * wn * exp(-adl / dl);
-                d = w * adl * sl * sg / (dl * dl);
-            }
-            sw += hh * w;
-            sd += hh * d;
+    const float zp32 = ldo<T>(a.z, o);
+    float zq[NT], nxq[NT], nyq[NT], nzq[NT], rq[NT], gq[NT], bq[NT], vq[NV], vz[NV];
+    bool in[NT], vin[NV];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                sc[k] += hh * w * cq[k];
-                sdc[k] += hh * d * cq[k];
-            }
+    for (int j = 0; j < NT; ++j) {
+        const int t = sub + L * j;
+        const int qx = x + (t % 5 - 2) * a.step, qy = y + (t / 5 - 2) * a.step;
+        in[j] = t < 25 && qx >= 0 && qx < a.w && qy >= 0 && qy < a.h;
+        const uint32_t q = in[j] ? (uint32_t)qy * (uint32_t)a.pitch + (uint32_t)qx : o;
+        zq[j] = ldo<T>(a.z, q);
+        nxq[j] = ldo<T>(a.nx, q);
+        nyq[j] = ldo<T>(a.ny, q);
+        nzq[j] = ldo<T>(a.nz, q);
+        rq[j] = ldo<T>(a.cr, q);
+        gq[j] = ldo<T>(a.cg, q);
+        bq[j] = ldo<T>(a.cb, q);
+    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int t = sub + L * j;
+        const int qx = x + t % 3 - 1, qy = y + t / 3 - 1;
+        vin[j] = t < 9 && qx >= 0 && qx < a.w && qy >= 0 && qy < a.h;
+        const uint32_t q = vin[j] ? (uint32_t)qy * (uint32_t)a.pitch + (uint32_t)qx : o;
+        vz[j] = ldo<T>(a.z, q);
+        vq[j] = ldf(a.var, q);
+    }
+    const double np_[3] = {ldo<T>(a.nx, o), ldo<T>(a.ny, o), ldo<T>(a.nz, o)};
+    const double gx = ldo<T>(a.dzdx, o), gy = ldo<T>(a.dzdy, o);
+    const double lp = luma_d(ldo<T>(a.cr, o), ldo<T>(a.cg, o), ldo<T>(a.cb, o));
+    const double kap = ldf(a.kappa, o);
+    if (empty_px(zp32)) return;
+    const double zp = zp32;
+    double gs = 0.0, gw = 0.0;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int t = sub + L * j;
+        if (!vin[j] || empty_px(vz[j])) continue;
+        const double k = (t % 3 == 1 ? 0.5 : 0.25) * (t / 3 == 1 ? 0.5 : 0.25);
+        gs += k * (double)vq[j];
+        gw += k;
+    }
+    const double sg = sqrt(px_sum(gs) / px_sum(gw));
+    const double sl = a.sigma_l;
+    const double dl = sl * kap * sg + (double)a.eps_l;
+    const double inv_dl = 1.0 / dl, dscale = sl * sg / (dl * dl);
+    double sw = 0.0, sd = 0.0, sc[3] = {0.0, 0.0, 0.0}, sdc[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int t = sub + L * j, aa = t % 5 - 2, b = t / 5 - 2;
+        if (!in[j] || (t != 12 && empty_px(zq[j]))) continue;
+        const double ha = aa == 0 ? 0.375 : aa * aa == 1 ? 0.25 : 0.0625;
+        const double hb = b == 0 ? 0.375 : b * b == 1 ? 0.25 : 0.0625;
+        const double hh = ha * hb;
+        const double cq[3] = {rq[j], gq[j], bq[j]};
+        double w = 1.0, d = 0.0;
+        if (t != 12) {
+            const double den = (double)a.sigma_z *
+                                   fabs(gx * (double)(a.step * aa) + gy * (double)(a.step * b)) +
+                               (double)a.eps_z;
+            const double ex = np_[0] - (double)nxq[j];
+            const double ey = np_[1] - (double)nyq[j];
+            const double ez = np_[2] - (double)nzq[j];
+            const double cs = 1.0 - 0.5 * (ex * ex + ey * ey + ez * ez);
+            // sigma_n log(cos), 0 where the normal weight is off
+            const double ln = a.sigma_n > 0.f ? (double)a.sigma_n * log(cs > 0.0 ? cs : 0.0) : 0.0;
+            const double adl = fabs(lp - luma_d(cq[0], cq[1], cq[2]));
+            w = exp(ln - fabs(zp - (double)zq[j]) / den - adl * inv_dl);
+            d = w * adl * dscale;
         }
+        sw += hh * w;
+        sd += hh * d;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            sc[k] += hh * w * cq[k];
+            sdc[k] += hh * d * cq[k];
+        }
+    }
+    sw = px_sum(sw);
+    sd = px_sum(sd);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        sc[k] = px_sum(sc[k]);
+        sdc[k] = px_sum(sdc[k]);
+    }
+    if (sub != 0) return;
     const double yy[3] = {ldf(a.yr, o), ldf(a.yg, o), ldf(a.yb, o)};
     const float *rp[3] = {a.rr, a.rg, a.rb};
     double g = 0.0;
@@ -591,7 +638,7 @@ extern "C" int sv_atrous_kappa_grad(const sv_rgb *c_in, const float *var_in, con
                     ref ? (const float *)ref->b : nullptr,
                     d_kappa, d.w, d.h, d.pitch, step, p->sigma_z, p->sigma_n, p->sigma_l,
                     p->eps_z, p->eps_l};
-    dim3 grid((d.w + 63) / 64, (d.h + 3) / 4);
+    dim3 grid((d.w + kKappaPx - 1) / kKappaPx, d.h);
     if (t == SV_F32)
         hipLaunchKernelGGL(kappa_grad_k<float>, grid, dim3(256), 0, as_stream(stream), a);
     else
