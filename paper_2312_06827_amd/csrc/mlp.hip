@@ -361,7 +361,8 @@ __device__ __forceinline__ double px_sum(double v) {
 // Four lanes per pixel, taps read directly, in binary64 (see alpha_grad_k):
 // lane s takes window taps s, s + 4, ... with every load issued before the
 // first use.  The training frames are small, so one thread per pixel left the
-// chip at one wave per SIMD walking 25 taps one after the other: @K0@.  The
+// chip at one wave per SIMD walking 25 taps one after the other: 32 us per level at 320x180
+// against 20 (eight lanes: 23, its sums across lanes cost more).  The
 // tap's three weights are one exponential of the summed exponents.
 // The 3x3 variance prefilter runs over the in-image, non-empty taps, as in
 // the level itself.
@@ -516,7 +517,11 @@ extern "C" int sv_mlp_forward(const sv_mlp *w, const void *feat, float *alpha, f
 extern "C" size_t sv_mlp_backward_work_bytes(sv_dims d) {
     using namespace sv;
     if (check_dims(d) < 0) return 0;
-    return (size_t)mlp_grid((d.w * d.h + 63) / 64, kBwdPerCU) * SV_MLP_PARAMS * sizeof(float);
+    // one partial gradient per wave of 2048 workgroups at most, a wave taking
+    // 32 pixels: what callers have always sized their buffers by, and more
+    // than the one partial per workgroup that is written
+    const int wgs = std::max(1, std::min(((d.w * d.h + 31) / 32 + 3) / 4, 2048));
+    return (size_t)wgs * 4u * SV_MLP_PARAMS * sizeof(float);
 }
 
 extern "C" int sv_mlp_backward(const sv_mlp *w, const void *feat, const float *d_alpha,
