@@ -247,14 +247,40 @@ def _planes3(x: Planes):
     return r, g, b
 
 
+def _stacked_ptrs(x: torch.Tensor, n: int):
+    """Pointers of the first n planes of a (.., H, W) device tensor from its
+    strides: the same as the views' own, without making a view per plane
+    (about 1.5 us each; a call passes a dozen planes)."""
+    if not x.is_cuda or x.stride(2) != 1 or x.numel() == 0:
+        return [_plane_ptr(x[i]) for i in range(n)]  # raises, or an empty plane's
+    p, s = x.data_ptr(), x.stride(0) * x.element_size()
+    return [p + i * s for i in range(n)]
+
+
 def _rgb(x: Planes) -> sv_rgb:
+    if isinstance(x, torch.Tensor) and x.dim() == 3 and x.shape[0] == 3:
+        return sv_rgb(*_stacked_ptrs(x, 3))
     r, g, b = _planes3(x)
     return sv_rgb(_plane_ptr(r), _plane_ptr(g), _plane_ptr(b))
 
 
+def _motion_ptrs(mv: Planes):
+    if isinstance(mv, torch.Tensor) and mv.dim() == 3 and mv.shape[0] >= 2:
+        return _stacked_ptrs(mv, 2)
+    return _plane_ptr(mv[0]), _plane_ptr(mv[1])
+
+
+def _lead(x: Planes) -> torch.Tensor:
+    """A tensor with the planes' dimensions and storage type: the colour
+    tensor itself, or the first of three planes."""
+    if isinstance(x, torch.Tensor) and x.dim() == 3 and x.shape[0] == 3:
+        return x
+    return _planes3(x)[0]
+
+
 def dims_of(t: torch.Tensor) -> sv_dims:
-    p = t if t.dim() == 2 else t[0]
-    return sv_dims(p.shape[1], p.shape[0], p.stride(0))
+    p = t if t.dim() in (2, 3) else t[0]
+    return sv_dims(p.shape[-1], p.shape[-2], p.stride(-2))
 
 
 def dtype_of(t: torch.Tensor) -> int:
@@ -281,9 +307,9 @@ class GBuf:
     id: Optional[torch.Tensor] = None
 
     def c(self) -> sv_gbuf:
-        nx, ny, nz = _planes3(self.n)
+        n = _rgb(self.n)
         return sv_gbuf(_plane_ptr(self.z), _plane_ptr(self.dzdx), _plane_ptr(self.dzdy),
-                       _plane_ptr(nx), _plane_ptr(ny), _plane_ptr(nz), _plane_ptr(self.id))
+                       n.r, n.g, n.b, _plane_ptr(self.id))
 
 
 @dataclass
@@ -347,7 +373,7 @@ class AtrousParams:
 
 def sv_tonemap(inp: Planes, out: Planes, inverse: bool = False, k: float = 1.0,
                weight: float = 1.0, mode: int = SV_TM_LUMA, stream=None):
-    r = _planes3(inp)[0]
+    r = _lead(inp)
     p = sv_tm_params(k, weight, mode)
     _check("sv_tonemap", load().sv_tonemap(
         ctypes.byref(_rgb(inp)), ctypes.byref(_rgb(out)), dims_of(r), dtype_of(r),
@@ -356,7 +382,7 @@ def sv_tonemap(inp: Planes, out: Planes, inverse: bool = False, k: float = 1.0,
 
 def sv_clamp(hist: Planes, cur: Planes, out: Planes, gamma: float,
              z: Optional[torch.Tensor] = None, stream=None):
-    r = _planes3(cur)[0]
+    r = _lead(cur)
     _check("sv_clamp", load().sv_clamp(
         ctypes.byref(_rgb(hist)), ctypes.byref(_rgb(cur)), ctypes.byref(_rgb(out)),
         _plane_ptr(z), dims_of(r), dtype_of(r), float(gamma), _stream(stream)))
@@ -364,7 +390,7 @@ def sv_clamp(hist: Planes, cur: Planes, out: Planes, gamma: float,
 
 def sv_clip(hist: Planes, cur: Planes, out: Planes, gamma: float,
             z: Optional[torch.Tensor] = None, stream=None):
-    r = _planes3(cur)[0]
+    r = _lead(cur)
     _check("sv_clip", load().sv_clip(
         ctypes.byref(_rgb(hist)), ctypes.byref(_rgb(cur)), ctypes.byref(_rgb(out)),
         _plane_ptr(z), dims_of(r), dtype_of(r), float(gamma), _stream(stream)))
@@ -383,9 +409,9 @@ def sv_temporal(cur: Planes, g: GBuf, mv: Planes, prev: GBuf, hist: Planes,
     network runs inside the step (needs albedo; alpha_map is ignored).
     With `var` (and its sv_variance workspace) the variance estimate's
     pointwise part is written here (finish with VarianceParams(listed=True))."""
-    mvx, mvy = mv[0], mv[1]
+    mvx, mvy = _motion_ptrs(mv)
     mc = None if mlp is None else mlp.c()
-    io = sv_temporal_io(_rgb(cur), g.c(), _plane_ptr(mvx), _plane_ptr(mvy), prev.c(),
+    io = sv_temporal_io(_rgb(cur), g.c(), mvx, mvy, prev.c(),
                         _rgb(hist), _plane_ptr(hist_m1), _plane_ptr(hist_m2c),
                         _plane_ptr(hist_n), _rgb(out), _plane_ptr(out_m1), _plane_ptr(out_m2c),
                         _plane_ptr(out_n), _plane_ptr(alpha_map),
@@ -393,7 +419,7 @@ def sv_temporal(cur: Planes, g: GBuf, mv: Planes, prev: GBuf, hist: Planes,
                         _rgb(albedo) if albedo is not None else sv_rgb(),
                         _plane_ptr(kappa_out), _plane_ptr(alpha_out), _plane_ptr(var),
                         None if var_work is None else var_work.data_ptr(), int(var_min_hist))
-    r = _planes3(cur)[0]
+    r = _lead(cur)
     pc = params.c()
     _check("sv_temporal", load().sv_temporal(ctypes.byref(io), dims_of(r), dtype_of(r),
                                              ctypes.byref(pc), _stream(stream)))
@@ -432,7 +458,7 @@ def sv_variance_noalloc(m1: torch.Tensor, m2c: torch.Tensor, n: torch.Tensor, g:
 def sv_atrous(c_in: Planes, var_in: torch.Tensor, g: GBuf, c_out: Planes,
               var_out: Optional[torch.Tensor], step: int, params: AtrousParams,
               kappa: Optional[torch.Tensor] = None, stream=None):
-    r = _planes3(c_in)[0]
+    r = _lead(c_in)
     gc = g.c()
     pc = params.c()
     _check("sv_atrous", load().sv_atrous(
@@ -445,7 +471,7 @@ def sv_atrous_sep(c_in: Planes, var_in: torch.Tensor, g: GBuf, scratch: Optional
                   c_out: Planes, var_out: Optional[torch.Tensor], step: int, params: AtrousParams,
                   kappa: Optional[torch.Tensor] = None, stream=None):
     """scratch None: both passes in one kernel (steps 1..16)."""
-    r = _planes3(c_in)[0]
+    r = _lead(c_in)
     gc = g.c()
     pc = params.c()
     sc = None if scratch is None else ctypes.byref(_rgb(scratch))
@@ -460,7 +486,7 @@ def sv_atrous_adaptive(c_in: Planes, var_in: torch.Tensor, g: GBuf, ctl: torch.T
                        var_out: Optional[torch.Tensor], level: int, separable: bool,
                        params: AtrousParams, kappa: Optional[torch.Tensor] = None, stream=None):
     """Level `level` with per-pixel control bytes `ctl` (uint8 plane)."""
-    r = _planes3(c_in)[0]
+    r = _lead(c_in)
     gc = g.c()
     pc = params.c()
     sc = None if scratch is None else ctypes.byref(_rgb(scratch))
@@ -512,7 +538,7 @@ def sv_temporal_gradient(prev: Planes, reshade: Planes, fmv: torch.Tensor, fz: t
     """alpha_map <- the blend factor raised where the previous frame's
     samples, traced again, changed.  pick and lam are (ceil(H/3), ceil(W/3))
     contiguous."""
-    r = _planes3(prev)[0]
+    r = _lead(prev)
     gc = g.c()
     p = sv_grad_params(alpha, tau_z, sigma_z, levels)
     _check("sv_temporal_gradient", load().sv_temporal_gradient(
@@ -525,7 +551,7 @@ def sv_temporal_gradient(prev: Planes, reshade: Planes, fmv: torch.Tensor, fz: t
 def sv_compose(direct: Planes, shadow: Optional[Planes], spec: Optional[Planes], out: Planes,
                stream=None):
     """out = direct * shadow + spec per colour channel."""
-    r = _planes3(direct)[0]
+    r = _lead(direct)
     opt = lambda p: None if p is None else ctypes.byref(_rgb(p))
     _check("sv_compose", load().sv_compose(
         ctypes.byref(_rgb(direct)), opt(shadow), opt(spec), ctypes.byref(_rgb(out)),
@@ -572,12 +598,12 @@ def sv_mlp_features(cur: Planes, g: GBuf, mv: Planes, prev: GBuf, hist: Planes,
                     hist_m1: torch.Tensor, hist_m2c: torch.Tensor, hist_n: torch.Tensor,
                     albedo: Planes, mlp: MLP, feat: torch.Tensor, params: TemporalParams,
                     hist_out: Optional[Planes] = None, stream=None):
-    r = _planes3(cur)[0]
+    r = _lead(cur)
     d = dims_of(r)
     if feat.numel() * feat.element_size() < d.w * d.h * 32 or not feat.is_contiguous():
         raise ValueError("feature buffer too small or not contiguous")
-    mvx, mvy = mv[0], mv[1]
-    io = sv_temporal_io(_rgb(cur), g.c(), _plane_ptr(mvx), _plane_ptr(mvy), prev.c(),
+    mvx, mvy = _motion_ptrs(mv)
+    io = sv_temporal_io(_rgb(cur), g.c(), mvx, mvy, prev.c(),
                         _rgb(hist), _plane_ptr(hist_m1), _plane_ptr(hist_m2c),
                         _plane_ptr(hist_n), sv_rgb(), None, None, None, None)
     pc, mc = params.c(), mlp.c()
@@ -625,7 +651,7 @@ def sv_adam(mlp: MLP, grad: torch.Tensor, lr=1e-3, beta1=0.9, beta2=0.999, eps=1
 def sv_mlp_alpha_grad(c_t: Planes, cur: Planes, hist: Planes, y: Planes, alpha: torch.Tensor,
                       n: torch.Tensor, z: torch.Tensor, d_alpha: torch.Tensor, tm_k: float = 1.0,
                       stream=None):
-    r = _planes3(c_t)[0]
+    r = _lead(c_t)
     _check("sv_mlp_alpha_grad", load().sv_mlp_alpha_grad(
         ctypes.byref(_rgb(c_t)), ctypes.byref(_rgb(cur)), ctypes.byref(_rgb(hist)),
         ctypes.byref(_rgb(y)), _plane_ptr(alpha), _plane_ptr(n), _plane_ptr(z), float(tm_k),
@@ -635,7 +661,7 @@ def sv_mlp_alpha_grad(c_t: Planes, cur: Planes, hist: Planes, y: Planes, alpha: 
 def sv_atrous_kappa_grad(c_in: Planes, var_in: torch.Tensor, g: GBuf, kappa: torch.Tensor,
                          y: Planes, d_kappa: torch.Tensor, step: int, params: AtrousParams,
                          ref: Optional[Planes] = None, stream=None):
-    r = _planes3(c_in)[0]
+    r = _lead(c_in)
     gc, pc = g.c(), params.c()
     rf = None if ref is None else ctypes.byref(_rgb(ref))
     _check("sv_atrous_kappa_grad", load().sv_atrous_kappa_grad(
