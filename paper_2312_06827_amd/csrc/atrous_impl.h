@@ -1126,6 +1126,22 @@ void launch_tile_py(const AtrousArgs &a, TileCfg cfg, hipStream_t s) {
                        dim3(per_xcd * kXCD), dim3(256), 0, s, a, tiles, per_xcd);
 }
 
+// Two lattice rows per thread pay only while their tiles fill the chip: a
+// frame of no more of them than CUs (at steps 2 and 4, whose tiles cost more
+// to stage, than one and a half times the CUs) takes one row per thread and
+// twice the workgroups.  Per level, one row against two, at 256x256 (128
+// tiles of two rows): 6.1 against 6.6 us (step 1), 6.0 against 7.3, 6.1
+// against 7.3 (step 4); at 480x270 (272): 8.5 against 7.9, 8.4 against 8.6,
+// 7.6 against 8.7; at 640x360 (450): 10.7 against 8.5, 9.8 against 9.2, 9.5
+// against 9.4.  (A batch plan runs all its streams' tiles as one list, by one
+// kernel, so it keeps the full-size choice.)
+template <int STEP>
+bool few_tiles(const AtrousArgs &a) {
+    if (recorder()) return false;
+    const int tiles = ((a.w + 63) / 64) * STEP * ((a.h + STEP * 8 - 1) / (STEP * 8));
+    return 2 * tiles <= (STEP == 1 ? 2 : 3) * kCUs;
+}
+
 // The tile height: the caller's choice for 5x5 levels up to step 16; at
 // step 32 (the adaptive level's coarser start) the 128-column tile with two
 // rows per thread (78 KB of LDS, as many workgroups per CU as the 64-column
@@ -1137,7 +1153,9 @@ void launch_tile(const AtrousArgs &a, TileCfg cfg, hipStream_t s) {
     } else if constexpr (DIR == kDir2D && STEP == 32) {  // the 128-column tile, two rows
         launch_tile_py<T, STEP, 2, MODE, WANT_VAR, DIR>(a, cfg, s);
     } else {
-        const int py = (DIR == kDir2D && STEP <= 16 && cfg.rows > 0) ? cfg.rows : tile_py(STEP);
+        const int py = (DIR == kDir2D && STEP <= 16 && cfg.rows > 0) ? cfg.rows
+                       : DIR == kDir2D && few_tiles<STEP>(a)         ? 1
+                                                                     : tile_py(STEP);
         if (py == 1) launch_tile_py<T, STEP, 1, MODE, WANT_VAR, DIR>(a, cfg, s);
         else launch_tile_py<T, STEP, (STEP <= 16 ? 2 : 1), MODE, WANT_VAR, DIR>(a, cfg, s);
     }

@@ -540,6 +540,23 @@ def test_atrous_sep_fused_equals_two_pass(H, W, dtype):
                 np.testing.assert_array_equal(res[1][1], res[0][1])
 
 
+@pytest.mark.parametrize("H,W,step", [(256, 512, 1), (256, 513, 1), (512, 384, 4), (512, 390, 4)])
+def test_atrous_small_frame_height_does_not_change_results(H, W, step):
+    """Either side of the line where a level takes one lattice row per thread
+    (256 two-row tiles at step 1, 384 at step 4): bitwise both heights."""
+    c, var, z, dzdx, dzdy, n = _atrous_inputs(H, W, 900 + step)
+    res = []
+    for rows in (0, 1, 2):
+        out, vout = empty_like_dev((3, H, W)), empty_like_dev((H, W))
+        say(f"atrous {H}x{W} step={step} rows={rows}")
+        L.sv_atrous(dev(c), dev(var), gbuf_dev(z, dzdx, dzdy, n), out, vout, step,
+                    L.AtrousParams(tile_rows=rows))
+        res.append((host(out), host(vout)))
+    for r in res[1:]:
+        np.testing.assert_array_equal(r[0], res[0][0])
+        np.testing.assert_array_equal(r[1], res[0][1])
+
+
 @pytest.mark.parametrize("H,W", [(37, 70), (130, 200)])
 def test_temporal_variance_listing_equals_variance_pass(H, W):
     """sv_temporal writing the variance's pointwise part and its list, then
