@@ -108,7 +108,8 @@ struct NormalCoef {
     float sn;    // sigma_n
     float snl;   // sigma_n log2(e)
     float umin;  // 0, or 1 when sigma_n == 0
-    int series;  // sigma_n >= kSeriesMinSigmaN: the a-trous levels use the series form
+    int series;  // sigma_n >= kSeriesMinSigmaN: the a-trous levels use the polynomial form
+    float q[5];  // the polynomial's coefficients, times sigma_n
 };
 
 __device__ __forceinline__ float add_normal_term(float e, float s2, const NormalCoef &k) {
@@ -119,35 +120,39 @@ __device__ __forceinline__ float add_normal_term(float e, float s2, const Normal
 }
 
 // From this sigma_n on, the a-trous levels take the normal term as a
-// truncated series (add_normal_series), with no logarithm.
+// polynomial (add_normal_poly), with no logarithm.
 constexpr float kSeriesMinSigmaN = 96.0f;
 
+// log2(1 - s2/2) / s2 on 0 <= s2 <= 0.22 to 7e-9 of itself: the polynomial of
+// degree 4 with the smallest largest relative error there (a weighted
+// least-squares fit, reweighted until the error is level).
+constexpr double kNormalPoly[5] = {-0.72134753, -0.18033577, -0.06015212, -0.02204816,
+                                   -0.01145215};
+
 inline NormalCoef make_normal_coef(float sigma_n) {
-    return NormalCoef{sigma_n, sigma_n * 1.4426950408889634f, sigma_n == 0.0f ? 1.0f : 0.0f,
-                      sigma_n >= kSeriesMinSigmaN ? 1 : 0};
+    NormalCoef k{sigma_n, sigma_n * 1.4426950408889634f, sigma_n == 0.0f ? 1.0f : 0.0f,
+                 sigma_n >= kSeriesMinSigmaN ? 1 : 0, {}};
+    for (int i = 0; i < 5; ++i) k.q[i] = (float)(kNormalPoly[i] * (double)sigma_n);
+    return k;
 }
 
-// The same term for large sigma_n without the logarithm.  With x = s2/2,
-// log2(1 - x) = -log2(e) (x + x^2/2 + ... + x^6/6 + R), taken through x^6/6
-// and evaluated by Horner in s2 (x^k/k = s2^k / (k 2^k)):
-//   sigma_n log2(1 - s2/2) ~ sigma_n s2 P(s2),  P(s2) = -log2(e) sum_k s2^(k-1) / (k 2^k).
-// The remainder R <= x^7 / (7 (1 - x)) is dropped; sigma_n R is the relative
-// error it leaves in the weight.  At sigma_n = 128 that stays below the
-// binary32 evaluation's own error (about 1e-6 relative) for every weight
-// above 1e-3 of the centre's and below 4e-6 for weights above 1e-6 (at 96:
-// 1.4e-6 and 1.5e-5), comparable to the log form's 5e-7 and 1.1e-6.  Where
-// x is large the series gives an exponentially small weight, as the exact
-// one is (or zero: for x >= 1 the exact weight is 0 and the series' exp2
-// underflows), so no clamp is needed; and no 1 - s2/2 is rounded, so no
-// residual term either.
-__device__ __forceinline__ float add_normal_series(float e, float s2, const NormalCoef &k) {
-    constexpr float L = 1.4426950408889634f;
-    float p = fmaf(s2, -L / 384.0f, -L / 160.0f);  // 1/(6 2^6), 1/(5 2^5)
-    p = fmaf(p, s2, -L / 64.0f);
-    p = fmaf(p, s2, -L / 24.0f);
-    p = fmaf(p, s2, -L / 8.0f);
-    p = fmaf(p, s2, -L / 2.0f);
-    return fmaf(p * s2, k.sn, e);
+// The same term for large sigma_n without the logarithm: sigma_n s2 Q(s2) by
+// Horner, sigma_n in the coefficients.  The polynomial's 7e-9 is below
+// binary32's own rounding for every weight above 1e-6 of the centre's at
+// sigma_n = 128 (s2 = 0.216 there; at 96, above 2.6e-5).  The Taylor sum
+// through (s2/2)^6 / 6, one term more, leaves 4e-6 at 1e-6.  Where s2 is
+// larger the polynomial gives an exponentially small weight, as the exact one
+// is (or zero: every coefficient is negative), so no clamp is needed; and no
+// 1 - s2/2 is rounded, so no residual term either.  Five instructions where
+// the sum and its scaling took seven: the five 5x5 levels of a 1080p frame
+// 253 -> 245 us (with sigma_n apart and literal coefficients 248, with the
+// coefficients held in vector registers 247).
+__device__ __forceinline__ float add_normal_poly(float e, float s2, const NormalCoef &k) {
+    float p = fmaf(k.q[4], s2, k.q[3]);
+    p = fmaf(p, s2, k.q[2]);
+    p = fmaf(p, s2, k.q[1]);
+    p = fmaf(p, s2, k.q[0]);
+    return fmaf(p, s2, e);
 }
 
 // The depth difference p's gradient (gx, gy) predicts over an offset

@@ -540,6 +540,47 @@ def test_atrous_sep_fused_equals_two_pass(H, W, dtype):
                 np.testing.assert_array_equal(res[1][1], res[0][1])
 
 
+@pytest.mark.parametrize("step", [1, 4, 8])
+def test_atrous_prefilter_beside_empty_and_signed_entries(step):
+    """The variance prefilter's quick sum and its per-entry form: an image
+    with lone empty pixels (their neighbours take the second form, the rest
+    the first) whose variance also holds zeros of either sign, against the
+    oracle; with the level's variance kept and without."""
+    H, W = 45, 139
+    c, var, z, dzdx, dzdy, n = _atrous_inputs(H, W, 950 + step)
+    z[5::11, 7::13] = 0.0
+    var[3::7, ::5] = 0.0
+    var[::6, 2::9] = -0.0
+    ro, rv = O.atrous(c, var, z, dzdx, dzdy, n, step)
+    for keep in (True, False):
+        out, vout = empty_like_dev((3, H, W)), empty_like_dev((H, W)) if keep else None
+        say(f"atrous prefilter step={step} variance kept {keep}")
+        L.sv_atrous(dev(c), dev(var), gbuf_dev(z, dzdx, dzdy, n), out, vout, step,
+                    L.AtrousParams())
+        assert rel_err(host(out), ro) <= TOL32
+        if keep:
+            assert rel_err(host(vout), rv) <= TOL32
+
+
+@pytest.mark.parametrize("sigma_n", [96.0, 128.0, 1000.0])
+def test_atrous_normal_polynomial_range(sigma_n):
+    """The polynomial normal term from its smallest sigma_n up, over normals
+    turned by up to 180 degrees across the window (chords from 0 to 2, far
+    beyond the range it is fitted on)."""
+    H, W = 37, 70
+    c, var, z, dzdx, dzdy, n = _atrous_inputs(H, W, 970)
+    r = np.random.default_rng(971)
+    ang = np.cumsum(r.choice([0.0, 0.01, 0.05, 0.2, 1.5], (H, W)), axis=1)
+    n = np.stack([np.sin(ang), np.cos(ang), np.zeros_like(ang)]).astype(np.float32)
+    out, vout = empty_like_dev((3, H, W)), empty_like_dev((H, W))
+    say(f"atrous sigma_n={sigma_n}")
+    L.sv_atrous(dev(c), dev(var), gbuf_dev(z, dzdx, dzdy, n), out, vout, 1,
+                L.AtrousParams(sigma_n=sigma_n))
+    ro, rv = O.atrous(c, var, z, dzdx, dzdy, n, 1, sigma_n=sigma_n)
+    assert rel_err(host(out), ro) <= TOL32
+    assert rel_err(host(vout), rv) <= TOL32
+
+
 @pytest.mark.parametrize("H,W,step", [(256, 512, 1), (256, 513, 1), (512, 384, 4), (512, 390, 4)])
 def test_atrous_small_frame_height_does_not_change_results(H, W, step):
     """Either side of the line where a level takes one lattice row per thread
