@@ -249,13 +249,14 @@ __device__ __forceinline__ bool tile_no_var(float e) { return __float_as_uint(e)
 // the fifth level, takes a wider tile instead (see TileShape).
 constexpr int tile_py(int step) { return step >= 8 ? 1 : 2; }
 
-template <int STEP, int PY, int DIR, bool WANT_VAR>
+template <int STEP, int PY, int DIR, bool WANT_VAR, int NT_>
 struct TileShape {
+    static constexpr int NT = NT_;  // threads of the workgroup
     // lattice columns: 64 (one wave per lattice row), or 128 at step 32,
     // where the column halo (2 x 64 pixels) would otherwise be staged for
     // every 64 outputs (two waves per lattice row there: 12 % faster)
     static constexpr int WX = (DIR == kDir2D && STEP == 32) ? 2 : 1;
-    static constexpr int TX = 64 * WX, RPP = 4 / WX, TY = RPP * PY;
+    static constexpr int TX = 64 * WX, RPP = NT / 64 / WX, TY = RPP * PY;
     static constexpr int HALO = DIR == kDir2DA ? 4 : 2;
     static constexpr int HY = DIR == kDirH ? 0 : HALO, HX = DIR == kDirV ? 0 : HALO * STEP;
     static constexpr int ROWS = TY + 2 * HY, COLS = TX + 2 * HX;
@@ -263,18 +264,18 @@ struct TileShape {
     static constexpr bool PF_TILE = STEP == 1 && (DIR == kDir2D || DIR == kDir2DA);
     static constexpr bool NEED_V = WANT_VAR || PF_TILE;
     static constexpr int PFC = TX + 2;
-    static constexpr int NS = ROWS * COLS, IT = (NS + 255) / 256;
+    static constexpr int NS = ROWS * COLS, IT = (NS + NT - 1) / NT;
     // prefilter rows staged per lattice row: the image rows above and below
     // it, and the row itself unless the tile already holds its variance
     // (with a column of halo on each side)
     static constexpr bool MID_TILE = !PF_TILE && NEED_V && HX >= 1;
     static constexpr int PFR = PF_TILE ? 0 : MID_TILE ? 2 : 3;
-    static constexpr int NP = TY * PFR * PFC, ITP = (NP + 255) / 256;
-    // LDS bytes of one workgroup, and the workgroups (one wave per SIMD
-    // each) that fit a CU's 160 KiB: the register budget is set to match,
-    // so registers never hold occupancy below what LDS allows
+    static constexpr int NP = TY * PFR * PFC, ITP = (NP + NT - 1) / NT;
+    // LDS bytes of one workgroup, and the waves per SIMD of the workgroups
+    // that fit a CU's 160 KiB: the register budget is set to match, so
+    // registers never hold occupancy below what LDS allows
     static constexpr int LDS = NS * 32 + (NEED_V ? NS * 4 : 4) + (NP > 0 ? NP * 4 : 4);
-    static constexpr int WAVES = 163840 / LDS < 8 ? 163840 / LDS : 8;
+    static constexpr int FIT = 163840 / LDS * (NT / 256), WAVES = FIT < 8 ? FIT : 8;
 };
 
 // Raw values of one tile held in registers between issue and LDS store.
@@ -304,7 +305,7 @@ __device__ __forceinline__ void tile_issue(const AtrousArgs &a, TileOrigin t, R 
     constexpr int STEP = S::HX == 0 ? 1 : S::HX / 2;  // only used for HX
 #pragma unroll
     for (int it = 0; it < S::IT; ++it) {
-        const int i = threadIdx.x + it * 256;
+        const int i = threadIdx.x + it * S::NT;
         const int r = i / S::COLS, c = i - r * S::COLS;
         const int gx = t.x0 - S::HX + c;
         const int gy = t.ybase + (r - S::HY) * a.step;
@@ -323,7 +324,7 @@ __device__ __forceinline__ void tile_issue(const AtrousArgs &a, TileOrigin t, R 
     (void)STEP;
 #pragma unroll
     for (int it = 0; it < S::ITP; ++it) {
-        const int i = threadIdx.x + it * 256;
+        const int i = threadIdx.x + it * S::NT;
         constexpr int PR = S::PFR > 0 ? S::PFR * S::PFC : 1;  // (no rows: no iteration)
         const int j = i / PR, rem = i - j * PR;
         const int rr = rem / S::PFC, c = rem - rr * S::PFC;
@@ -342,7 +343,7 @@ __device__ __forceinline__ void tile_store(const R &g, float4 *s_cl, float4 *s_g
                                            float *s_pf) {
 #pragma unroll
     for (int it = 0; it < S::IT; ++it) {
-        const int i = threadIdx.x + it * 256;
+        const int i = threadIdx.x + it * S::NT;
         if (i < S::NS) {
             const bool ok = g.in[it] && !empty_px(g.z[it]);
             s_cl[i] = ok ? make_float4(g.r[it], g.g[it], g.b[it], luma(g.r[it], g.g[it], g.b[it]))
@@ -354,16 +355,16 @@ __device__ __forceinline__ void tile_store(const R &g, float4 *s_cl, float4 *s_g
     }
 #pragma unroll
     for (int it = 0; it < S::ITP; ++it) {
-        const int i = threadIdx.x + it * 256;
+        const int i = threadIdx.x + it * S::NT;
         if (i < S::NP) s_pf[i] = (g.pin[it] && !empty_px(g.pz[it])) ? g.pv[it] : kNoVar;
     }
 }
 
-template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR>
+template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR, int NT>
 __device__ __forceinline__ void tile_compute(const AtrousArgs &a, TileOrigin t,
                                              const float4 *s_cl, const float4 *s_gn,
                                              const float *s_v, const float *s_pf) {
-    using S = TileShape<STEP, PY, DIR, WANT_VAR>;
+    using S = TileShape<STEP, PY, DIR, WANT_VAR, NT>;
     constexpr int COLS = S::COLS, HY = S::HY, HX = S::HX, PFC = S::PFC;
     const int lx = (int)threadIdx.x % S::TX, ly = (int)threadIdx.x / S::TX;
     const int x = t.x0 + lx;
@@ -500,10 +501,10 @@ __device__ __forceinline__ void tile_compute(const AtrousArgs &a, TileOrigin t,
     }
 }
 
-template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR, bool PERSIST>
-__global__ __launch_bounds__(256) __attribute__((
-    amdgpu_waves_per_eu(TileShape<STEP, PY, DIR, WANT_VAR>::WAVES))) void atrous_tile_k(AtrousArgs a, int tiles, int per_xcd) {
-    using S = TileShape<STEP, PY, DIR, WANT_VAR>;
+template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR, int NT, bool PERSIST>
+__global__ __launch_bounds__(NT) __attribute__((
+    amdgpu_waves_per_eu(TileShape<STEP, PY, DIR, WANT_VAR, NT>::WAVES))) void atrous_tile_k(AtrousArgs a, int tiles, int per_xcd) {
+    using S = TileShape<STEP, PY, DIR, WANT_VAR, NT>;
     __shared__ float4 s_cl[S::NS];  // r, g, b, L (L = +inf: no tap)
     __shared__ float4 s_gn[S::NS];  // z, nx, ny, nz (z = 0: no tap)
     __shared__ float s_v[S::NEED_V ? S::NS : 1];
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(256) __attribute__((
         tile_issue<T, S>(a, o, regs);
         tile_store<S>(regs, s_cl, s_gn, s_v, s_pf);
         __syncthreads();
-        tile_compute<T, STEP, PY, MODE, WANT_VAR, DIR>(a, o, s_cl, s_gn, s_v, s_pf);
+        tile_compute<T, STEP, PY, MODE, WANT_VAR, DIR, NT>(a, o, s_cl, s_gn, s_v, s_pf);
         return;
     }
     tile_issue<T, S>(a, tile_origin<STEP, S::TY, S::TX>(t, gxt), regs);
@@ -537,7 +538,7 @@ __global__ __launch_bounds__(256) __attribute__((
     for (;;) {
         const int tn = t + nslot;
         if (tn < last) tile_issue<T, S>(a, tile_origin<STEP, S::TY, S::TX>(tn, gxt), regs);
-        tile_compute<T, STEP, PY, MODE, WANT_VAR, DIR>(a, tile_origin<STEP, S::TY, S::TX>(t, gxt),
+        tile_compute<T, STEP, PY, MODE, WANT_VAR, DIR, NT>(a, tile_origin<STEP, S::TY, S::TX>(t, gxt),
                                                        s_cl, s_gn, s_v, s_pf);
         if (tn >= last) break;
         __syncthreads();
@@ -549,11 +550,11 @@ __global__ __launch_bounds__(256) __attribute__((
 
 // Batched form: the tiles of many streams (each its own AtrousArgs), one
 // tile per workgroup; every tile is staged and computed exactly as above.
-template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR>
-__global__ __launch_bounds__(256) __attribute__((
-    amdgpu_waves_per_eu(TileShape<STEP, PY, DIR, WANT_VAR>::WAVES))) void atrous_batch_k(const AtrousArgs *args, const int *prefix,
+template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR, int NT>
+__global__ __launch_bounds__(NT) __attribute__((
+    amdgpu_waves_per_eu(TileShape<STEP, PY, DIR, WANT_VAR, NT>::WAVES))) void atrous_batch_k(const AtrousArgs *args, const int *prefix,
                                                       int n, int total) {
-    using S = TileShape<STEP, PY, DIR, WANT_VAR>;
+    using S = TileShape<STEP, PY, DIR, WANT_VAR, NT>;
     __shared__ float4 s_cl[S::NS];
     __shared__ float4 s_gn[S::NS];
     __shared__ float s_v[S::NEED_V ? S::NS : 1];
@@ -572,13 +573,13 @@ __global__ __launch_bounds__(256) __attribute__((
     tile_issue<T, S>(a, o, regs);
     tile_store<S>(regs, s_cl, s_gn, s_v, s_pf);
     __syncthreads();
-    tile_compute<T, STEP, PY, MODE, WANT_VAR, DIR>(a, o, s_cl, s_gn, s_v, s_pf);
+    tile_compute<T, STEP, PY, MODE, WANT_VAR, DIR, NT>(a, o, s_cl, s_gn, s_v, s_pf);
 }
 
-template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR>
+template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR, int NT>
 void atrous_batch_launch(const void *args, const int *prefix, int n, int total, hipStream_t s) {
-    hipLaunchKernelGGL((atrous_batch_k<T, STEP, PY, MODE, WANT_VAR, DIR>), dim3(xcd_grid(total)),
-                       dim3(256), 0, s, (const AtrousArgs *)args, prefix, n, total);
+    hipLaunchKernelGGL((atrous_batch_k<T, STEP, PY, MODE, WANT_VAR, DIR, NT>),
+                       dim3(xcd_grid(total)), dim3(NT), 0, s, (const AtrousArgs *)args, prefix, n, total);
 }
 
 // ---- 5x5 level, direct loads (any step) -------------------------------------
@@ -1110,26 +1111,26 @@ struct TileCfg {
     int rows;
 };
 
-template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR>
+template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR, int NT = 256>
 void launch_tile_py(const AtrousArgs &a, TileCfg cfg, hipStream_t s) {
-    using S = TileShape<STEP, PY, DIR, WANT_VAR>;
+    using S = TileShape<STEP, PY, DIR, WANT_VAR, NT>;
     constexpr int TY = S::TY;
     const int bands = (a.h + STEP * TY - 1) / (STEP * TY);
     const int tiles = ((a.w + S::TX - 1) / S::TX) * bands * STEP;
     const int per_xcd = (tiles + kXCD - 1) / kXCD;
-    if (record_pass(&atrous_batch_launch<T, STEP, PY, MODE, WANT_VAR, DIR>, a, tiles)) return;
+    if (record_pass(&atrous_batch_launch<T, STEP, PY, MODE, WANT_VAR, DIR, NT>, a, tiles)) return;
     // the adaptive level's wider tile leaves no registers for a prefetched
-    // next tile: it always runs one tile per workgroup
-    if constexpr (DIR != kDir2DA) {
+    // next tile, nor do 512 threads: one tile per workgroup there
+    if constexpr (DIR != kDir2DA && NT == 256) {
         if (cfg.persistent) {
             const int slots = min(per_xcd, kCUs / kXCD * max(1, cfg.blocks_per_cu));
-            hipLaunchKernelGGL((atrous_tile_k<T, STEP, PY, MODE, WANT_VAR, DIR, true>),
-                               dim3(slots * kXCD), dim3(256), 0, s, a, tiles, per_xcd);
+            hipLaunchKernelGGL((atrous_tile_k<T, STEP, PY, MODE, WANT_VAR, DIR, NT, true>),
+                               dim3(slots * kXCD), dim3(NT), 0, s, a, tiles, per_xcd);
             return;
         }
     }
-    hipLaunchKernelGGL((atrous_tile_k<T, STEP, PY, MODE, WANT_VAR, DIR, false>),
-                       dim3(per_xcd * kXCD), dim3(256), 0, s, a, tiles, per_xcd);
+    hipLaunchKernelGGL((atrous_tile_k<T, STEP, PY, MODE, WANT_VAR, DIR, NT, false>),
+                       dim3(per_xcd * kXCD), dim3(NT), 0, s, a, tiles, per_xcd);
 }
 
 // Two lattice rows per thread pay only while their tiles fill the chip: a
@@ -1148,16 +1149,19 @@ bool few_tiles(const AtrousArgs &a) {
     return 2 * tiles <= (STEP == 1 ? 2 : 3) * kCUs;
 }
 
-// The tile height: the caller's choice for 5x5 levels up to step 16; at
-// step 32 (the adaptive level's coarser start) the 128-column tile with two
-// rows per thread (78 KB of LDS, as many workgroups per CU as the 64-column
-// one-row tile); tile_py otherwise.
+// The tile height: the caller's choice for 5x5 levels up to step 16, else
+// tile_py.  The adaptive level and step 32 (its coarser start) stage halos of
+// the doubled step, 41 to 78 KB of LDS a tile: their tiles are shared by 512
+// threads of one lattice row each, where 256 threads of two rows left a CU
+// two or three waves per SIMD.  Adaptive levels of two 1080p streams, 256 ->
+// 512 threads: 119 -> 99 us (step 1), 124 -> 109, 159 -> 124, 155 -> 122
+// (step 8); step 32 of a 1365x767 frame 46 -> 35.  (The plain steps 8 and 16,
+// four and five waves per SIMD with 256 threads of one row, lose with twice
+// the rows: 48 -> 51 and 55 us at 1080p.)
 template <typename T, int STEP, int MODE, bool WANT_VAR, int DIR>
 void launch_tile(const AtrousArgs &a, TileCfg cfg, hipStream_t s) {
-    if constexpr (DIR == kDir2DA) {  // two rows per thread (measured best at every step)
-        launch_tile_py<T, STEP, 2, MODE, WANT_VAR, DIR>(a, cfg, s);
-    } else if constexpr (DIR == kDir2D && STEP == 32) {  // the 128-column tile, two rows
-        launch_tile_py<T, STEP, 2, MODE, WANT_VAR, DIR>(a, cfg, s);
+    if constexpr (DIR == kDir2DA || (DIR == kDir2D && STEP == 32)) {
+        launch_tile_py<T, STEP, 1, MODE, WANT_VAR, DIR, 512>(a, cfg, s);
     } else {
         const int py = (DIR == kDir2D && STEP <= 16 && cfg.rows > 0) ? cfg.rows
                        : DIR == kDir2D && few_tiles<STEP>(a)         ? 1
