@@ -244,10 +244,10 @@ __global__ __launch_bounds__(256, 2) void mlp_backward_k(MlpArgs a) {
 // Sum of the nw partial gradients, one parameter per column.  A workgroup
 // owns 16 columns (one 64-byte piece of every partial) and splits the rows
 // over 64 groups of lanes, whose sums a tree in LDS joins in a fixed order.
-// One thread per parameter walking all rows put the whole sum, up to 8192
-// dependent loads, on seven workgroups: latency alone, 1910 us at 1920x1080
-// and 420 us at 320x180 against 5 and 4 us now (of 2048 and 900 partials: 24 and 7 of 8192 and 1800).  Shorter chains also
-// round less.
+// One thread per parameter walking all rows put the whole sum on seven
+// workgroups, each thread one chain of loads: of 8192 partials at 1920x1080
+// 1910 us and of 1800 at 320x180 420 us, against 24 and 7; of the 512 and 225
+// partials there are now, 5 and 4.  Shorter chains also round less.
 constexpr int kRedCols = 16, kRedRows = 64;
 
 __global__ __launch_bounds__(kRedCols *kRedRows) void mlp_reduce_k(const float *part, int nw,
