@@ -72,15 +72,22 @@ __global__ __launch_bounds__(256) void mlp_forward_k(MlpArgs a) {
 // The weight gradients are contractions over pixels, so their operands hold
 // pixels along K: lane l gives eight pixels of unit l % 32.  An operand with
 // units along K, taken as A against a unit matrix as B, leaves exactly that
-// in the accumulators (one product by 1 and zeros: exact), so the activations
-// and the back-propagated gradients are turned on the matrix cores instead of
-// through LDS.  Every value that is rounded to bfloat16 is formed as in a
-// plain backward pass; 26 matrix instructions per 32 pixels, no LDS stores
-// and no barrier in the loop.At 1920x1080
+// in the accumulators (one product by 1 and zeros: exact for finite values),
+// so the activations and the back-propagated gradients are turned on the
+// matrix cores instead of through LDS.  Every value that is rounded to
+// bfloat16 is formed as in a plain backward pass; 26 matrix instructions per
+// 32 pixels, no LDS stores and no barrier in the loop.  At 1920x1080
 // 99 us against 242 us for the form that turned four 32 x 32 tiles a block
 // through 2-byte LDS stores and rounded in software.  The chain of dependent
 // products at two waves per SIMD (256 registers) bounds it: with both of a
 // wave's blocks in flight it spills, 176 us, and one wave per SIMD hides less.
+//
+// A value that is not finite, times the unit matrix's zeros, is NaN in every
+// unit of its pixel, and so in every sum that the pixel enters.  A wave whose
+// sums come out that way therefore runs its blocks again with the operands
+// turned through LDS, which moves values without arithmetic: a NaN feature
+// then reaches its own column of W1's gradient, and a head gradient that is
+// not finite the units that it flows through.
 
 // What the backward pass holds beside NetW.
 struct BwdW {
@@ -108,11 +115,73 @@ __device__ __forceinline__ void load_bwd(const uint16_t *wq, int lane, BwdW &b) 
     b.unit_g = as_operand(u32x4{col == 16 ? kOne : col == 17 ? kOne << 16 : 0u, 0u, 0u, 0u});
 }
 
+// A wave's tile in LDS, 32 units x 32 pixels (row pitch 36: fewer bank
+// conflicts), and the order of its stores and loads: LDS serves a wave's
+// accesses in order, so only the compiler has to keep them so.
+constexpr int kTurnPitch = 36;
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Row lane % 32 of the tile as the operand pair.
+__device__ __forceinline__ void turn_read(const uint16_t *t, int lane, bf16x8 (&out)[2]) {
+    const uint2 *row = (const uint2 *)(t + (lane & 31) * kTurnPitch);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const uint2 a = row[4 * j + (lane >> 5)], b = row[4 * j + 2 + (lane >> 5)];
+        out[j] = as_operand(u32x4{a.x, a.y, b.x, b.y});
+    }
+}
+
+__device__ __forceinline__ void turn_store(uint16_t *t, int lane, int j, bf16x8 v) {
+    const u32x4 d = __builtin_bit_cast(u32x4, v);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        t[drow(8 * j + i, lane >> 5) * kTurnPitch + (lane & 31)] = (uint16_t)(d[i / 2] >> (i % 2 * 16));
+}
+
 // The operand pair (units along K) with its pixels along K instead.
-__device__ __forceinline__ f32x16 turned(const BwdW &w, const bf16x8 (&v)[2]) {
-    f32x16 d = {};
-    d = mfma16(v[0], w.unit[0], d);
-    return mfma16(v[1], w.unit[1], d);
+template <bool LDS>
+__device__ __forceinline__ void turn(const BwdW &w, uint16_t *t, int lane, const bf16x8 (&v)[2],
+                                     bf16x8 (&out)[2]) {
+    if constexpr (LDS) {
+        turn_store(t, lane, 0, v[0]);
+        turn_store(t, lane, 1, v[1]);
+        wave_order();
+        turn_read(t, lane, out);
+        wave_order();
+    } else {
+        f32x16 d = {};
+        d = mfma16(v[0], w.unit[0], d);
+        d = mfma16(v[1], w.unit[1], d);
+        out[0] = pack_operand(d, 0);
+        out[1] = pack_operand(d, 1);
+    }
+}
+
+// The features in columns 0..15 and the head gradients in 16 and 17, pixels
+// along K (`g` counts in the lower half of the wave only).
+template <bool LDS>
+__device__ __forceinline__ void turn_xg(const BwdW &w, uint16_t *t, int lane, bf16x8 x, uint32_t g,
+                                        bf16x8 (&out)[2]) {
+    if constexpr (LDS) {
+        turn_store(t, lane, 0, x);
+        if (lane < 32) {
+            t[16 * kTurnPitch + lane] = (uint16_t)g;
+            t[17 * kTurnPitch + lane] = (uint16_t)(g >> 16);
+        }
+        wave_order();
+        turn_read(t, lane, out);
+        wave_order();
+        if ((lane & 31) >= 18) out[0] = out[1] = as_operand(u32x4{});
+    } else {
+        f32x16 d = {};
+        d = mfma16(x, w.unit[0], d);
+        d = mfma16(as_operand(u32x4{lane < 32 ? g : 0u, 0u, 0u, 0u}), w.unit_g, d);
+        out[0] = pack_operand(d, 0);
+        out[1] = pack_operand(d, 1);
+    }
 }
 
 // Sum over the 32 lanes of one half-wave (butterfly, fixed order).
@@ -129,9 +198,10 @@ struct BwdAcc {
 };
 
 // One 32-pixel block: g holds the two head gradients of pixel lane % 32 in
-// bfloat16, in both halves of the wave; `first` in the lower one.
-__device__ __forceinline__ void backward_block(const NetW &f, const BwdW &w, bf16x8 x,
-                                               const FwdOut &r, uint32_t g, bool first,
+// bfloat16, in both halves of the wave.
+template <bool LDS>
+__device__ __forceinline__ void backward_block(const NetW &f, const BwdW &w, uint16_t *t, int lane,
+                                               bf16x8 x, const FwdOut &r, uint32_t g,
                                                BwdAcc &acc) {
     const float g0 = __uint_as_float(g << 16), g1 = __uint_as_float(g & 0xFFFF0000u);
     f32x16 gh2;
@@ -150,37 +220,28 @@ __device__ __forceinline__ void backward_block(const NetW &f, const BwdW &w, bf1
         acc.db1[i] += gh1[i];
     }
     const bf16x8 g1b[2] = {pack_operand(gh1, 0), pack_operand(gh1, 1)};
-    // features in columns 0..15, the head gradients in 16 and 17
-    f32x16 xg = {};
-    xg = mfma16(x, w.unit[0], xg);
-    xg = mfma16(as_operand(u32x4{first ? g : 0u, 0u, 0u, 0u}), w.unit_g, xg);
-    const f32x16 g1t = turned(w, g1b), g2t = turned(w, gb), h1t = turned(w, r.h1),
-                 h2t = turned(w, r.h2);
+    bf16x8 xg[2], g1t[2], g2t[2], h1t[2], h2t[2];
+    turn_xg<LDS>(w, t, lane, x, g, xg);
+    turn<LDS>(w, t, lane, g1b, g1t);
+    turn<LDS>(w, t, lane, gb, g2t);
+    turn<LDS>(w, t, lane, r.h1, h1t);
+    turn<LDS>(w, t, lane, r.h2, h2t);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const bf16x8 xgo = pack_operand(xg, j);
-        acc.dw1 = mfma16(pack_operand(g1t, j), xgo, acc.dw1);
-        acc.dw2 = mfma16(pack_operand(g2t, j), pack_operand(h1t, j), acc.dw2);
-        acc.dw3 = mfma16(pack_operand(h2t, j), xgo, acc.dw3);
+        acc.dw1 = mfma16(g1t[j], xg[j], acc.dw1);
+        acc.dw2 = mfma16(g2t[j], h1t[j], acc.dw2);
+        acc.dw3 = mfma16(h2t[j], xg[j], acc.dw3);
     }
 }
 
-__global__ __launch_bounds__(256, 2) void mlp_backward_k(MlpArgs a) {
-    __shared__ float s_part[4][SV_MLP_PARAMS];
-    __shared__ u32x4 s_w[kNetStage];
-    __shared__ __align__(16) float s_b[kNetFloats];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// A wave's blocks of 32 pixels.
+template <bool LDS>
+__device__ __forceinline__ void backward_wave(const MlpArgs &a, NetW &f, const BwdW &w,
+                                              const float *s_b, uint16_t *t, int lane, int wave,
+                                              BwdAcc &acc) {
     const int col = lane & 31, hf = lane >> 5;
-    NetStage ns;
-    net_issue(a.params, a.wq, ns);
-    net_store(ns, s_w, s_b);
-    BwdW w;
-    load_bwd(a.wq, lane, w);
-    __syncthreads();
-    NetW f;
-    load_operands(s_w, lane, f);
-    BwdAcc acc = {};
     const int nblk = (a.npix + 31) / 32;
+    acc = {};
     for (int blk = blockIdx.x * 4 + wave; blk < nblk; blk += gridDim.x * 4) {
         const int p = blk * 32 + col;
         const bool valid = p < a.npix;
@@ -210,11 +271,33 @@ __global__ __launch_bounds__(256, 2) void mlp_backward_k(MlpArgs a) {
             acc.db3a += g0;
             acc.db3b += g1;
         }
-        backward_block(f, w, x, r, pack_bf16(g0, g1), hf == 0, acc);
+        backward_block<LDS>(f, w, t, lane, x, r, pack_bf16(g0, g1), acc);
     }
+}
+
+__global__ __launch_bounds__(256, 2) void mlp_backward_k(MlpArgs a) {
+    __shared__ __align__(16) float s_part[4][SV_MLP_PARAMS];
+    __shared__ u32x4 s_w[kNetStage];
+    __shared__ __align__(16) float s_b[kNetFloats];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = lane & 31, hf = lane >> 5;
+    NetStage ns;
+    net_issue(a.params, a.wq, ns);
+    net_store(ns, s_w, s_b);
+    BwdW w;
+    load_bwd(a.wq, lane, w);
+    __syncthreads();
+    NetW f;
+    load_operands(s_w, lane, f);
+    BwdAcc acc;
+    float *sp = s_part[wave];
+    backward_wave<false>(a, f, w, s_b, nullptr, lane, wave, acc);
+    // a value that was not finite is in every element of its sums (above)
+    const float any = acc.dw1[0] * 0.f + acc.dw2[0] * 0.f + acc.dw3[0] * 0.f;
+    if (__any(!(any == 0.f)))
+        backward_wave<true>(a, f, w, s_b, (uint16_t *)sp, lane, wave, acc);
     // this workgroup's partial gradient, flat order: the four waves' sums
     // joined in LDS
-    float *sp = s_part[wave];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int u = drow(i, hf);

@@ -154,6 +154,59 @@ def test_backward_of_repeated_pixels(reps, N):
     assert np.all(err <= allow), (int(np.argmax(err - allow)), float((err - allow).max()))
 
 
+@pytest.mark.parametrize("kind", ["feature", "alpha", "kappa"])
+def test_backward_keeps_non_finite_values_apart(kind):
+    """A pixel with a NaN feature has no hidden activation (max(NaN, 0) is 0
+    here): it reaches its own column of W1's gradient and nothing else.  A
+    head gradient that is not finite reaches its own row of W3 and the units
+    that it flows through.  Every other entry is the oracle's."""
+    N = 300  # ten blocks of 32 pixels, the last one ragged
+    w = _weights(90)
+    r = np.random.default_rng(91)
+    xs = M.bf16(r.normal(0, 1.2, (14, N)))
+    da, dk = M.f32(r.normal(0, 1.0, N)), M.f32(r.normal(0, 1.0, N))
+    dead = np.zeros(M.N_PARAMS, bool)  # entries that are not finite
+    part = M.Weights.from_flat(dead, w.mu, w.inv_s)  # the same, by layer
+    dx, dda, ddk = xs.copy(), da.copy(), dk.copy()
+    off = np.zeros(N, bool)  # pixels without hidden activations
+    if kind == "feature":
+        for p, k in ((0, 3), (37, 0), (130, 13), (N - 1, 3)):
+            dx[k, p] = np.nan
+            off[p] = True
+            part.w1[:, k] = 1
+    else:
+        fw = M.forward(w, xs, bf16_ops=True)
+        row, d, dd = (0, da, dda) if kind == "alpha" else (1, dk, ddk)
+        for p, v in ((5, np.inf), (38, np.nan)):
+            dd[p], d[p] = v, 0.0
+            u2, u1 = fw["a2"][:, p] > 0, fw["a1"][:, p] > 0
+            part.w3[row], part.b3[row] = 1, 1
+            part.w2[u2], part.b2[u2], part.w1[u1], part.b1[u1] = 1, 1, 1, 1
+    dead = part.flat() != 0
+    assert 0 < dead.sum() < dead.size
+    grad = torch.empty(L.SV_MLP_PARAMS, device="cuda")
+    like = torch.empty((1, N), device="cuda")
+    rows = np.zeros((N, 16), np.float32)
+    rows[:, :14] = dx.T
+    feat = torch.from_numpy(rows).to(torch.bfloat16).view(torch.int16).cuda()
+    say(f"mlp backward, not finite: {kind}")
+    L.sv_mlp_backward(_device_mlp(w), feat, dev(dda[None]), dev(ddk[None]), grad,
+                      L.mlp_workspace(like), like)
+    # the pixels without activations as a network whose first layer is off
+    w_off = M.Weights.from_flat(w.flat(), w.mu, w.inv_s)
+    w_off.w1, w_off.b1 = 0.0 * w.w1, 0.0 * w.b1
+    ref, allow = np.zeros(M.N_PARAMS), np.zeros(M.N_PARAMS)
+    for net, pick in ((w, ~off), (w_off, off)):
+        if pick.any():
+            _, _, bg, asum, total, _ = B.flip_bounds(net, xs[:, pick], da[pick], dk[pick])
+            ref += total
+            allow += bg + 2.0 ** -16 * asum
+    got = host(grad)
+    np.testing.assert_array_equal(~np.isfinite(got), dead)
+    err = np.abs(got - ref)[~dead]
+    assert np.all(err <= allow[~dead]), float((err - allow[~dead]).max())
+
+
 def test_adam_parity():
     r = np.random.default_rng(3)
     p0 = M.f32(r.normal(0, 1, L.SV_MLP_PARAMS))
