@@ -291,15 +291,16 @@ __device__ __forceinline__ void variance_spatial_stream(const VarianceArgs &a, u
         for (int j = 0; j < PER; ++j) {
             const int t = sub + 8 * j;
             const int dx = t % D - R, dy = t / D - R;
+            // an empty pixel enters no sum, whatever moments it holds
+            ok[j] = ok[j] && (t == CTR || !empty_px(zq[j]));
             float w;
             if (t == CTR) {
                 w = 1.f;
             } else {
                 const float s2 = chord2(nxp, nyp, nzp, qx_[j], qy_[j], qz_[j]);
                 const float kz = spatial_depth_scale(a, gx, gy, dx, dy);
-                w = empty_px(zq[j]) ? 0.f : spatial_weight(a, zc - zq[j], kz, s2);
+                w = spatial_weight(a, zc - zq[j], kz, s2);
             }
-            w = ok[j] ? w : 0.f;
             wt[j] = w;
             if (ok[j]) {
                 sw += w;

@@ -337,6 +337,63 @@ def test_variance_dense_tiles_equal_the_list(H, W, radius, dtype):
         np.testing.assert_array_equal(got[pick], full[pick], err_msg=str(count))
 
 
+def _dense_inputs(H, W, radius):
+    """Moments and G-buffer with empty pixels in three of four tiles, and a
+    function giving exactly `count` live short pixels in every tile that has
+    as many (all of them elsewhere)."""
+    r = np.random.default_rng(720 + H + radius)
+    z, dzdx, dzdy, n = random_gbuf(r, H, W)
+    tile = np.arange(H)[:, None] // 4 * ((W + 63) // 64) + np.arange(W)[None, :] // 64
+    z[(r.random((H, W)) < 0.05) & (tile % 4 != 3)] = 0.0
+    m1 = r.uniform(0.1, 1.0, (H, W)).astype(np.float32)
+    m2c = (m1 * m1 * r.uniform(0.0, 1.0, (H, W))).astype(np.float32)
+    order = r.random((H, W))
+
+    def short(count):
+        pick = np.zeros((H, W), bool)
+        for t in range(tile.max() + 1):
+            idx = np.flatnonzero((tile == t) & (z > 0))
+            pick.flat[idx[np.argsort(order.flat[idx])][:count]] = True
+        sizes = np.bincount(tile[pick])
+        assert (sizes == count).any(), "a tile with this many short pixels"
+        return pick
+
+    def run(hn, m1=m1, m2c=m2c):
+        work = L.variance_workspace(empty_like_dev((H, W)))
+        out = empty_like_dev((H, W), W + 3)
+        L.sv_variance(dev(m1, W + 3), dev(m2c, W + 3), dev(hn, W + 3, torch.uint8),
+                      gbuf_dev(z, dzdx, dzdy, n, W + 3), out, L.VarianceParams(radius=radius),
+                      work)
+        assert list_consumed(work)
+        return host(out)
+
+    def oracle(hn):
+        return O.variance(m1, m2c.astype(np.float64) + m1.astype(np.float64) ** 2, hn, z, dzdx,
+                          dzdy, n, radius=radius)
+
+    return z, m1, m2c, short, run, oracle
+
+
+@pytest.mark.parametrize("radius", [0, 2, 3, 7])
+def test_variance_forms_leave_empty_moments_out(radius):
+    """The window holds non-empty pixels only: moments of empty pixels that
+    are not finite enter neither form, at exact counts of live short pixels
+    per 64x4 tile either side of the line between the forms (65) and up to a
+    whole tile."""
+    H, W = 37, 330
+    z, m1, m2c, short, run, oracle = _dense_inputs(H, W, radius)
+    bad = np.array([np.nan, np.inf, -np.inf], np.float32)
+    where = np.flatnonzero(z == 0)
+    h1, h2 = m1.copy(), m2c.copy()
+    h1.flat[where], h2.flat[where] = bad[where % 3], bad[where // 3 % 3]
+    say(f"variance with moments of empty pixels not finite, radius {radius}")
+    for count in (1, 63, 64, 65, 66, 100, 129, 255, 256):
+        hn = np.where(short(count), 1, 12).astype(np.uint8)
+        got = run(hn, h1, h2)
+        assert rel_err(got, oracle(hn)) <= TOL32, count
+        np.testing.assert_array_equal(got, run(hn), err_msg=str(count))
+
+
 def test_variance_workspace_across_sizes():
     """One workspace, sized for the largest frame, serves calls of any
     smaller size in any order: the list of one call never leaks into the
