@@ -110,14 +110,15 @@ __device__ __forceinline__ float dense_estimate(const VarianceArgs &a, const flo
     for (int j = 0; j < PER; ++j) {
         const int t = q + 4 * j;
         const int dx = t % D - R, dy = t / D - R;
-        const bool ok = t < NT;
-        const int i = ok ? ci + dy * S::COLS + dx : ci;
+        // past the window: the empty entry after the tile's
+        const int i = t < NT ? ci + dy * S::COLS + dx : S::N;
         const float2 m = s_m[i];
         const float4 g = s_g[i];
         const float v =
             spatial_weight(a, pg.x - g.x, spatial_depth_scale(a, gx, gy, dx, dy),
                            chord2(pg.y, pg.z, pg.w, g.y, g.z, g.w));
-        w[j] = t == CTR ? 1.f : ok && g.x < INFINITY ? v : 0.f;
+        // an empty tap's -0 adds nothing, and marks it for the second loop
+        w[j] = t == CTR ? 1.f : g.x < INFINITY ? v : -0.f;
         m1[j] = m.x;
         sw[j & 1] += w[j];
         s1[j & 1] = fmaf(w[j], m.x, s1[j & 1]);
@@ -132,8 +133,8 @@ __device__ __forceinline__ float dense_estimate(const VarianceArgs &a, const flo
     s1[0] = s1[1] = 0.f;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const float d = m1[j] - mean1;
-        s1[j & 1] = q + 4 * j < NT ? fmaf(w[j] * d, d, s1[j & 1]) : s1[j & 1];
+        const float d = m1[j] - mean1;  // may be infinite: not to be times a 0
+        s1[j & 1] = signbit(w[j]) ? s1[j & 1] : fmaf(w[j] * d, d, s1[j & 1]);
     }
     return fmaxf(0.f, (mom + join(s1)) / sum);
 }
@@ -167,6 +168,10 @@ __device__ __forceinline__ void variance_dense_tile(const VarianceArgs &a, int t
             s_g[i] = ok ? make_float4(z, nx, ny, nz) : make_float4(INFINITY, 0.f, 0.f, 0.f);
             s_m[i] = ok ? make_float2(m1, m2) : make_float2(0.f, 0.f);
         }
+    }
+    if (threadIdx.x == 0) {
+        s_g[S::N] = make_float4(INFINITY, 0.f, 0.f, 0.f);
+        s_m[S::N] = make_float2(0.f, 0.f);
     }
     s_d[threadIdx.x] = make_float2(gx, gy);
     __syncthreads();
@@ -344,8 +349,8 @@ __global__ __launch_bounds__(256) void variance_spatial_batch_k(const VarianceAr
 // a time.
 template <typename T, int R>
 __global__ __launch_bounds__(256, 4) void variance_short_k(VarianceArgs a, int dense) {
-    __shared__ float4 s_g[DenseShape<R>::N];
-    __shared__ float2 s_m[DenseShape<R>::N], s_d[256];
+    __shared__ float4 s_g[DenseShape<R>::N + 1];
+    __shared__ float2 s_m[DenseShape<R>::N + 1], s_d[256];
     __shared__ uint8_t s_px[256], s_flag[256];
     __shared__ uint32_t wave_n[4];
     const int b = (int)blockIdx.x, nslot = dense / kXCD;

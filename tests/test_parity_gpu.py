@@ -394,6 +394,26 @@ def test_variance_forms_leave_empty_moments_out(radius):
         np.testing.assert_array_equal(got, run(hn), err_msg=str(count))
 
 
+@pytest.mark.parametrize("radius", [0, 1, 3, 6])
+def test_variance_forms_agree_on_infinite_moments(radius):
+    """A live pixel whose second moment is infinite (binary32 overflow of
+    the squared luminance) has an infinite variance in either form, and the
+    forms agree where the weighted sums overflow."""
+    H, W = 37, 330
+    z, m1, m2c, short, run, _ = _dense_inputs(H, W, radius)
+    few, listed = short(1), short(64)
+    inf = m2c.copy()
+    inf[few] = np.inf
+    for what, h1, h2 in (("moments", m1, inf), ("sums", np.full_like(m1, 2e38), m2c)):
+        say(f"variance with infinite {what}, radius {radius}")
+        got = run(np.where(listed, 1, 12).astype(np.uint8), h1, h2)
+        if what == "moments":
+            assert np.isposinf(got[few]).all()
+        for count in (65, 200, 256):
+            dense = run(np.where(short(count), 1, 12).astype(np.uint8), h1, h2)
+            np.testing.assert_array_equal(dense[listed], got[listed], err_msg=f"{what} {count}")
+
+
 def test_variance_workspace_across_sizes():
     """One workspace, sized for the largest frame, serves calls of any
     smaller size in any order: the list of one call never leaks into the
