@@ -235,8 +235,10 @@ inline uint32_t point_grid(sv_dims d) {
 
 // Appends this thread's pixel (x, y) if `spatial`: one atomic per
 // workgroup.  Every thread of the 256-thread workgroup must call it (it
-// holds two barriers); tile is this workgroup's 64x4 tile index.
-__device__ __forceinline__ void list_short_pixel(VarWork *work, uint32_t cap, int tile,
+// holds two barriers); tile is this workgroup's 64x4 tile index.  A tile of
+// more than MOST such pixels is not listed: true is returned (to all).
+template <uint32_t MOST = kVX * kVY>
+__device__ __forceinline__ bool list_short_pixel(VarWork *work, uint32_t cap, int tile,
                                                  bool spatial, int x, int y, uint32_t *wave_n,
                                                  uint32_t &base_sh) {
     const uint64_t mask = __ballot(spatial);
@@ -249,7 +251,8 @@ __device__ __forceinline__ void list_short_pixel(VarWork *work, uint32_t cap, in
     __syncthreads();
     const uint32_t n0 = wave_n[0], n1 = wave_n[1], n2 = wave_n[2], n3 = wave_n[3];
     const uint32_t total = n0 + n1 + n2 + n3;
-    if (total == 0) return;  // uniform over the workgroup
+    if (total > MOST) return true;   // uniform over the workgroup,
+    if (total == 0) return false;    // and so is this
     const uint32_t k = (uint32_t)tile % kXCD;
     if (threadIdx.x == 0)
         base_sh = atomicAdd(&work->count[k * kLines + kCount], total) -
@@ -259,6 +262,7 @@ __device__ __forceinline__ void list_short_pixel(VarWork *work, uint32_t cap, in
     const uint32_t slot = base_sh + before + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
     // a workspace that was not zeroed cannot push a store past the sublist
     if (spatial && slot < cap) work->list[k * cap + slot] = ((uint32_t)y << 15) | (uint32_t)x;
+    return false;
 }
 
 // ---- batched passes (many independent streams, one launch per pass) ----------

@@ -6,8 +6,9 @@
 // Pass 1 (pointwise) writes the temporal estimate and lists the pixels
 // whose history is short, except in tiles that hold many of them; pass 2
 // computes the spatial estimate of the listed pixels, eight lanes per pixel,
-// spread over every CU, and of the dense tiles from LDS.  (Where the temporal
-// step has written the first part, it has listed every short pixel.)
+// spread over every CU, and of the dense tiles, from LDS where there are many.
+// (Where the temporal step has written the first part, it has listed every
+// short pixel.)
 #include <algorithm>
 #include <mutex>
 
@@ -51,9 +52,8 @@ __device__ __forceinline__ bool variance_point_px(const VarianceArgs &a, int til
 
 // Depth scale of an offset: the same for (dx, dy) and (-dx, -dy), bit for bit.
 __device__ __forceinline__ float spatial_depth_scale(const VarianceArgs &a, float gx, float gy,
-                                                     int dx, int dy) {
-    const float den =
-        fmaf(a.sigma_z, fabsf(grad_offset(gx, gy, (float)dx, (float)dy)), a.eps_z);
+                                                     float dx, float dy) {
+    const float den = fmaf(a.sigma_z, fabsf(grad_offset(gx, gy, dx, dy)), a.eps_z);
     return kLog2e / den;
 }
 
@@ -66,7 +66,8 @@ __device__ __forceinline__ float spatial_weight(const VarianceArgs &a, float dz,
 
 // ---- dense tiles ---------------------------------------------------------------
 //
-// A tile with at least kDenseTile short pixels is computed by one workgroup:
+// A tile with at least kDenseTile short pixels is not listed but marked.  Many
+// of them are computed by one workgroup each:
 // its window, (64 + 2 R) x (4 + 2 R) pixels of depth, normal and moments, is
 // staged once in LDS, and the short pixels are packed onto the threads.  Every
 // value is then loaded about 2.7 times (R = 3) where the listed form gathers
@@ -75,19 +76,42 @@ __device__ __forceinline__ float spatial_weight(const VarianceArgs &a, float dz,
 // result does not depend on which form computed it.  An empty or outside pixel
 // is staged with an infinite depth, which marks it: its weight is 0.
 // A quarter of a tile: below it the list is as fast, and its pixels spread over
-// the whole chip.  Measured at 1920x1080, binary32, the call with its short
-// pixels in 16x16 patches (everything listed -> dense tiles): 2 % short 23 ->
-// 24 us, 20 % 126 -> 90, 50 % 245 -> 115, all 415 -> 155 (there the pointwise
-// pass went from 79 to 8 us: a listing tile takes an atomic, and those of a
-// sublist run one after the other).
+// the whole chip.  In a frame of up to kScanWords words of marks (2048 tiles),
+// up to 96 dense tiles (R <= 4, see dense_blocks) take the listed form as well,
+// straight from the marks: a workgroup per tile leaves most of the chip idle there, while in a
+// larger frame the list hides it and counting the marks (2 to 3 us at 8160
+// tiles) is the loss.
+// The call with its short pixels in 16x16 patches, binary32, R = 3, everything
+// listed -> as here: at 1920x1080 none short 8.5 -> 9.5 us, 2 % 24.8 -> 24.9,
+// 20 % 128 -> 94, all 454 -> 151 (there the pointwise pass goes from 79 to 7 us:
+// a listing tile takes an atomic, and those of a sublist run one after the
+// other); at 256x256 none 4.5 -> 4.9, 10 % 8.0 -> 10.0 (with the LDS form for
+// every dense tile 10.4), all 17.8 -> 13.6.
 constexpr uint32_t kDenseTile = 65;
-constexpr int kDenseBlocks = 768;  // workgroups that share the dense tiles
+constexpr int kScanWords = 512;    // words of marks, four tiles each, up to which they are counted
 
-// The pointwise pass leaves one word per tile, dense or not, at the end of the
-// tile's sublist (tile % 8), where no entry of it can be: a sublist has 256
-// words per tile, and a tile lists fewer than kDenseTile pixels.
-__device__ __forceinline__ uint32_t flag_word(uint32_t cap, int tile) {
-    return (uint32_t)tile % kXCD * cap + cap - 1u - (uint32_t)tile / kXCD;
+// The pointwise pass leaves one byte per tile, dense or not, at the end of
+// the last sublist, where no entry of it can be: a sublist has 1024 bytes per
+// tile of its own, and a tile lists fewer than kDenseTile pixels.  Before the
+// marks, on a line of their own (in the counters' line they slowed its atomics
+// down: the pass took 60 us for 36), three words tell whether there is a mark:
+//   kTurn   a number, written by the reading pass of the last call,
+//   kCall   the next one, this call's, and
+//   kDense  that of the last call that had a dense tile,
+// the last two written by the pointwise pass.  Whatever an earlier use of the
+// workspace left there, a call's own dense tile is seen, and at worst marks
+// are counted that do not exist.
+constexpr int kTurn = 0, kCall = 1, kDense = 2;
+
+__device__ __forceinline__ int tile_count(const VarianceArgs &a) {
+    return ((a.w + kVX - 1) / kVX) * ((a.h + kVY - 1) / kVY);
+}
+__device__ __forceinline__ uint32_t *dense_marks(const VarianceArgs &a) {
+    return a.work->list + kXCD * a.cap - (tile_count(a) + 3) / 4;
+}
+__device__ __forceinline__ uint32_t *dense_words(const VarianceArgs &a) {
+    const uint32_t marks = kXCD * a.cap - (uint32_t)((tile_count(a) + 3) / 4);
+    return a.work->list + ((marks - kLines) & ~(kLines - 1u));
 }
 
 template <int R>
@@ -108,15 +132,14 @@ __device__ __forceinline__ float dense_estimate(const VarianceArgs &a, const flo
     float w[PER], m1[PER], sw[2] = {0.f, 0.f}, s1[2] = {0.f, 0.f}, sm[2] = {0.f, 0.f};
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int t = q + 4 * j;
-        const int dx = t % D - R, dy = t / D - R;
+        const int t = q + 4 * j, dx = t % D - R, dy = t / D - R;
         // past the window: the empty entry after the tile's
         const int i = t < NT ? ci + dy * S::COLS + dx : S::N;
         const float2 m = s_m[i];
         const float4 g = s_g[i];
-        const float v =
-            spatial_weight(a, pg.x - g.x, spatial_depth_scale(a, gx, gy, dx, dy),
-                           chord2(pg.y, pg.z, pg.w, g.y, g.z, g.w));
+        const float v = spatial_weight(a, pg.x - g.x,
+                                       spatial_depth_scale(a, gx, gy, (float)dx, (float)dy),
+                                       chord2(pg.y, pg.z, pg.w, g.y, g.z, g.w));
         // an empty tap's -0 adds nothing, and marks it for the second loop
         w[j] = t == CTR ? 1.f : g.x < INFINITY ? v : -0.f;
         m1[j] = m.x;
@@ -131,10 +154,18 @@ __device__ __forceinline__ float dense_estimate(const VarianceArgs &a, const flo
     };
     const float sum = join(sw), mean1 = join(s1) / sum, mom = join(sm);
     s1[0] = s1[1] = 0.f;
+    if (R < 6 && fabsf(mean1) < INFINITY) {  // (R = 6 spills with both loops)
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const float d = m1[j] - mean1;  // may be infinite: not to be times a 0
-        s1[j & 1] = signbit(w[j]) ? s1[j & 1] : fmaf(w[j] * d, d, s1[j & 1]);
+        for (int j = 0; j < PER; ++j) {
+            const float d = m1[j] - mean1;
+            s1[j & 1] = fmaf(w[j] * d, d, s1[j & 1]);
+        }
+    } else {  // an empty tap's 0 times d may be NaN
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const float d = m1[j] - mean1;
+            s1[j & 1] = signbit(w[j]) ? s1[j & 1] : fmaf(w[j] * d, d, s1[j & 1]);
+        }
     }
     return fmaxf(0.f, (mom + join(s1)) / sum);
 }
@@ -185,11 +216,12 @@ __device__ __forceinline__ void variance_dense_tile(const VarianceArgs &a, int t
     if (spatial)
         s_px[before + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] = (uint8_t)threadIdx.x;
     __syncthreads();
-    const int q = threadIdx.x & 3;
     for (uint32_t k = threadIdx.x / 4; k < total; k += 64) {  // whole groups of four
         const int px = s_px[k], lx = px & 63, ly = px >> 6;
         const float2 d = s_d[px];
-        const float v = dense_estimate<R>(a, s_g, s_m, (ly + R) * S::COLS + lx + R, d.x, d.y, q);
+        const int q = threadIdx.x & 3;
+        const float v =
+            dense_estimate<R>(a, s_g, s_m, (ly + R) * S::COLS + lx + R, d.x, d.y, q);
         if (q == 0)
             stf(a.var, (uint32_t)(byt * kVY + ly) * (uint32_t)a.pitch + (uint32_t)(bxt * kVX + lx),
                 v);
@@ -201,13 +233,19 @@ __device__ __forceinline__ void variance_dense_tile(const VarianceArgs &a, int t
 template <typename T>
 __global__ __launch_bounds__(256) void variance_point_k(VarianceArgs a) {
     __shared__ uint32_t wave_n[4], base_sh;
-    const int gxt = (a.w + kVX - 1) / kVX;
-    const int tile = xcd_tile(gxt * ((a.h + kVY - 1) / kVY));
+    const int gxt = (a.w + kVX - 1) / kVX, tile = xcd_tile(tile_count(a));
     int x, y;
     const bool spatial = variance_point_px<T>(a, tile, tile % gxt, tile / gxt, x, y);
-    const bool dense = (uint32_t)__syncthreads_count(spatial) >= kDenseTile;  // uniform
-    if (tile >= 0 && threadIdx.x == 0) a.work->list[flag_word(a.cap, tile)] = dense ? 1u : 0u;
-    list_short_pixel(a.work, a.cap, tile, spatial && !dense, x, y, wave_n, base_sh);
+    const bool dense = list_short_pixel<kDenseTile - 1>(a.work, a.cap, tile, spatial, x, y,
+                                                        wave_n, base_sh);
+    if (tile < 0 || threadIdx.x != 0) return;
+    ((uint8_t *)dense_marks(a))[tile] = dense;
+    if (dense || tile == 0) {
+        uint32_t *words = dense_words(a);
+        const uint32_t call = words[kTurn] + 1u;
+        if (tile == 0) words[kCall] = call;
+        if (dense) words[kDense] = call;
+    }
 }
 
 template <typename T>
@@ -243,89 +281,114 @@ __device__ __forceinline__ float group8_sum(float v) {
     return v;
 }
 
-// Window of radius R, eight lanes per listed pixel: lane `sub` takes taps
-// sub, sub + 8, ...  Every tap's loads are issued before any weight is
-// formed, and the weights and m1 stay in registers for the second pass.
-template <typename T, int R>
-__device__ __forceinline__ void variance_spatial_stream(const VarianceArgs &a, uint32_t b, uint32_t blocks) {
+// The spatial estimate of pixel (x, y), in the image, by eight lanes: lane
+// `sub` takes taps sub, sub + 8, ...  Every tap's loads are issued before any
+// weight is formed, and the weights and m1 stay in registers for the second
+// pass.  TEST: the pixel may be one that needs no estimate.
+template <typename T, int R, bool TEST = false>
+__device__ __forceinline__ void spatial_estimate(const VarianceArgs &a, int x, int y, int sub) {
     constexpr int D = 2 * R + 1, NT = D * D, PER = (NT + 7) / 8, CTR = R * D + R;
-    uint32_t pre[kXCD + 1];
+    const uint32_t po = (uint32_t)y * (uint32_t)a.pitch + (uint32_t)x;
+    const float zc = ldo<T>(a.z, po), gx = ldo<T>(a.dzdx, po), gy = ldo<T>(a.dzdy, po);
+    const float nxp = ldo<T>(a.nx, po), nyp = ldo<T>(a.ny, po), nzp = ldo<T>(a.nz, po);
+    const int n = TEST ? a.n[po] : 0;
+    float zq[PER], qx_[PER], qy_[PER], qz_[PER], m1q[PER], m2q[PER];
+    bool ok[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int t = sub + 8 * j;
+        const int dx = t % D - R, dy = t / D - R;
+        const int qx = x + dx, qy = y + dy;
+        ok[j] = t < NT && qx >= 0 && qx < a.w && qy >= 0 && qy < a.h;
+        const uint32_t q = vofs(ok[j] ? (uint32_t)qy * (uint32_t)a.pitch + (uint32_t)qx : po);
+        zq[j] = ldo<T>(a.z, q);
+        qx_[j] = ldo<T>(a.nx, q);
+        qy_[j] = ldo<T>(a.ny, q);
+        qz_[j] = ldo<T>(a.nz, q);
+        m1q[j] = ldf(a.m1, q);
+        m2q[j] = ldf(a.m2c, q);
+    }
+    if (TEST && !(n >= 1 && n < a.min_hist && !empty_px(zc))) return;  // all eight lanes
+    // pass 1: weights and weighted sums of m1 and m2c
+    float wt[PER];
+    float sw = 0.f, s1 = 0.f, sm = 0.f;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int t = sub + 8 * j;
+        const int dx = t % D - R, dy = t / D - R;
+        // an empty pixel enters no sum, whatever moments it holds
+        ok[j] = ok[j] && (t == CTR || !empty_px(zq[j]));
+        float w;
+        if (t == CTR) {
+            w = 1.f;
+        } else {
+            const float s2 = chord2(nxp, nyp, nzp, qx_[j], qy_[j], qz_[j]);
+            const float kz = spatial_depth_scale(a, gx, gy, (float)dx, (float)dy);
+            w = spatial_weight(a, zc - zq[j], kz, s2);
+        }
+        wt[j] = w;
+        if (ok[j]) {
+            sw += w;
+            s1 = fmaf(w, m1q[j], s1);
+            sm = fmaf(w, m2q[j], sm);
+        }
+    }
+    sw = group8_sum(sw);
+    s1 = group8_sum(s1);
+    sm = group8_sum(sm);
+    const float mean1 = s1 / sw;
+    // pass 2: spread of m1 about its weighted mean
+    float spread = 0.f;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const float d = m1q[j] - mean1;
+        if (ok[j]) spread = fmaf(wt[j] * d, d, spread);
+    }
+    spread = group8_sum(spread);
+    if (sub == 0) stf(a.var, po, fmaxf(0.f, (sm + spread) / sw));
+}
+
+// Where the sublists start when laid end to end (pre[kXCD]: all entries).
+__device__ __forceinline__ void list_starts(const VarianceArgs &a, uint32_t (&pre)[kXCD + 1]) {
     pre[0] = 0;
 #pragma unroll
     for (int k = 0; k < kXCD; ++k)
         pre[k + 1] = pre[k] + min(a.work->count[k * kLines + kCount] -
                                       a.work->count[k * kLines + kBase],
                                   a.cap);
-    const uint32_t count = pre[kXCD];
-    // the list is consumed: the next appending pass starts after it (no
-    // workgroup of this pass reads kNext)
+}
+
+// Pixel e of the list; false for a stale entry outside the image.
+__device__ __forceinline__ bool list_pixel(const VarianceArgs &a, const uint32_t (&pre)[kXCD + 1],
+                                           uint32_t e, int &x, int &y) {
+    int k = 0;
+#pragma unroll
+    for (int j = 1; j < kXCD; ++j) k += e >= pre[j] ? 1 : 0;
+    const uint32_t packed = a.work->list[k * a.cap + (e - pre[k])];
+    x = (int)(packed & 32767u), y = (int)(packed >> 15);
+    return x < a.w && y < a.h;
+}
+
+// The list is consumed: the next appending pass starts after it (no
+// workgroup of this pass reads kNext).
+__device__ __forceinline__ void list_done(const VarianceArgs &a, uint32_t b) {
     if (b == 0 && threadIdx.x < kXCD)
         a.work->count[threadIdx.x * kLines + kNext] = a.work->count[threadIdx.x * kLines + kCount];
-    const int sub = threadIdx.x & 7;
-    const uint32_t groups = blocks * (blockDim.x / 8);
-    for (uint32_t e = b * (blockDim.x / 8) + (threadIdx.x >> 3); e < count; e += groups) {
-        int k = 0;
-#pragma unroll
-        for (int j = 1; j < kXCD; ++j) k += e >= pre[j] ? 1 : 0;
-        const uint32_t packed = a.work->list[k * a.cap + (e - pre[k])];
-        const int x = (int)(packed & 32767u), y = (int)(packed >> 15);
-        if (x >= a.w || y >= a.h) continue;  // only a stale entry can be outside
-        const uint32_t po = (uint32_t)y * (uint32_t)a.pitch + (uint32_t)x;
-        const float zc = ldo<T>(a.z, po), gx = ldo<T>(a.dzdx, po), gy = ldo<T>(a.dzdy, po);
-        const float nxp = ldo<T>(a.nx, po), nyp = ldo<T>(a.ny, po), nzp = ldo<T>(a.nz, po);
-        float zq[PER], qx_[PER], qy_[PER], qz_[PER], m1q[PER], m2q[PER];
-        bool ok[PER];
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int t = sub + 8 * j;
-            const int dx = t % D - R, dy = t / D - R;
-            const int qx = x + dx, qy = y + dy;
-            ok[j] = t < NT && qx >= 0 && qx < a.w && qy >= 0 && qy < a.h;
-            const uint32_t q = vofs(ok[j] ? (uint32_t)qy * (uint32_t)a.pitch + (uint32_t)qx : po);
-            zq[j] = ldo<T>(a.z, q);
-            qx_[j] = ldo<T>(a.nx, q);
-            qy_[j] = ldo<T>(a.ny, q);
-            qz_[j] = ldo<T>(a.nz, q);
-            m1q[j] = ldf(a.m1, q);
-            m2q[j] = ldf(a.m2c, q);
-        }
-        // pass 1: weights and weighted sums of m1 and m2c
-        float wt[PER];
-        float sw = 0.f, s1 = 0.f, sm = 0.f;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int t = sub + 8 * j;
-            const int dx = t % D - R, dy = t / D - R;
-            // an empty pixel enters no sum, whatever moments it holds
-            ok[j] = ok[j] && (t == CTR || !empty_px(zq[j]));
-            float w;
-            if (t == CTR) {
-                w = 1.f;
-            } else {
-                const float s2 = chord2(nxp, nyp, nzp, qx_[j], qy_[j], qz_[j]);
-                const float kz = spatial_depth_scale(a, gx, gy, dx, dy);
-                w = spatial_weight(a, zc - zq[j], kz, s2);
-            }
-            wt[j] = w;
-            if (ok[j]) {
-                sw += w;
-                s1 = fmaf(w, m1q[j], s1);
-                sm = fmaf(w, m2q[j], sm);
-            }
-        }
-        sw = group8_sum(sw);
-        s1 = group8_sum(s1);
-        sm = group8_sum(sm);
-        const float mean1 = s1 / sw;
-        // pass 2: spread of m1 about its weighted mean
-        float spread = 0.f;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const float d = m1q[j] - mean1;
-            if (ok[j]) spread = fmaf(wt[j] * d, d, spread);
-        }
-        spread = group8_sum(spread);
-        if (sub == 0) stf(a.var, po, fmaxf(0.f, (sm + spread) / sw));
+}
+
+constexpr int kGroups = 256 / 8;  // pixels of a workgroup at a time
+
+template <typename T, int R, bool ANEW = false>
+__device__ __forceinline__ void variance_spatial_stream(const VarianceArgs &a, uint32_t b,
+                                                        uint32_t blocks) {
+    uint32_t pre[kXCD + 1];
+    list_starts(a, pre);
+    list_done(a, b);
+    int x, y;
+    for (uint32_t e = b * kGroups + threadIdx.x / 8; e < pre[kXCD]; e += blocks * kGroups) {
+        // ANEW: nothing about the lane's taps is kept from pixel to pixel
+        const int sub = ANEW ? (int)vofs(threadIdx.x & 7) : threadIdx.x & 7;
+        if (list_pixel(a, pre, e, x, y)) spatial_estimate<T, R>(a, x, y, sub);
     }
 }
 
@@ -341,39 +404,104 @@ __global__ __launch_bounds__(256) void variance_spatial_batch_k(const VarianceAr
     variance_spatial_stream<T, R>(a, blockIdx.x, gridDim.x);
 }
 
-// The second pass after variance_point_k: the workgroups of the dense tiles
-// and the list's, side by side, so that few dense tiles hide behind the list.
-// (Within the pointwise pass their latency came on top of the list's: 27 us
-// instead of 22 with 2 % of the pixels short.)  A dense workgroup walks a
-// strided run of its XCD's contiguous range of tiles, their marks read 256 at
-// a time.
+// The second pass after variance_point_k: the first `dense` workgroups for the
+// dense tiles, then the list's, side by side, so that few dense tiles hide
+// behind the list and many fill the chip before it (workgroups of the two kinds
+// in turn left half of the CUs without tiles: all pixels of 1920x1080 short 275
+// us for 157).  Where no tile is dense they end on one load of two words.
+// Registers: as many waves per SIMD as the listed form alone has, or one fewer
+// (R = 4 and 5), without spilling.  Capped at four for every R, R = 4 to 7
+// spilled 26 to 346 registers: 1920x1080, 2 % of the pixels short, R = 5 65 us
+// and R = 7 185, now 34 and 61 (everything listed: 32 and 55); all short 507
+// and 1802, now 340 and 872 (728 and 1422).
+template <int R>
+constexpr int short_waves() { return R <= 3 ? 4 : R == 4 ? 3 : R <= 6 ? 2 : 1; }
+// One to three workgroups a CU, no more than are resident at once (R = 7, none
+// short, 1920x1080: 11.6 us with three).  A multiple of kXCD.
+template <int R>
+constexpr int dense_blocks() { return 256 * std::min(short_waves<R>(), 3); }
+
 template <typename T, int R>
-__global__ __launch_bounds__(256, 4) void variance_short_k(VarianceArgs a, int dense) {
-    __shared__ float4 s_g[DenseShape<R>::N + 1];
-    __shared__ float2 s_m[DenseShape<R>::N + 1], s_d[256];
-    __shared__ uint8_t s_px[256], s_flag[256];
+__global__ __launch_bounds__(256, short_waves<R>()) void variance_short_k(
+    VarianceArgs a, int dense) {
+    using S = DenseShape<R>;
+    __shared__ float4 s_g[S::N + 1];
+    __shared__ float2 s_m[S::N + 1], s_d[256];
+    __shared__ uint32_t s_before[256];
+    __shared__ uint8_t s_px[256];
     __shared__ uint32_t wave_n[4];
-    const int b = (int)blockIdx.x, nslot = dense / kXCD;
+    const int b = (int)blockIdx.x;
+    uint32_t *const state = dense_words(a);
     if (b >= dense) {
-        variance_spatial_stream<T, R>(a, (uint32_t)(b - dense), kSpatialBlocks);
+        const uint32_t call = state[kCall];
+        // (R = 6 would spill 2 registers in binary16)
+        variance_spatial_stream<T, R, R == 6>(a, (uint32_t)(b - dense),
+                                              gridDim.x - (uint32_t)dense);
+        // (a store before the list's loads would make them vector loads)
+        if (b == dense && threadIdx.x == 0) state[kTurn] = call;
         return;
     }
-    const int tiles = ((a.w + kVX - 1) / kVX) * ((a.h + kVY - 1) / kVY);
-    const int per = (tiles + kXCD - 1) / kXCD;
-    const int first = b % kXCD * per, last = min(tiles, first + per);
-    for (int base = first + b / kXCD; base < last; base += 256 * nslot) {
-        const int mine = base + (int)threadIdx.x * nslot;
-        const bool flag = mine < last && a.work->list[flag_word(a.cap, mine)] != 0u;
-        if (!__syncthreads_or(flag)) continue;  // uniform
-        s_flag[threadIdx.x] = flag;
-        __syncthreads();
-        for (int k = 0; k < 256 && base + k * nslot < last; ++k) {
-            if (!s_flag[k]) continue;  // uniform
-            variance_dense_tile<T, R>(a, base + k * nslot, s_g, s_m, s_d, s_px, wave_n);
-            __syncthreads();  // the next tile stages over this one
+    if (state[kDense] != state[kCall]) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int tiles = tile_count(a), words = (tiles + 3) / 4;
+    const uint32_t *marks = dense_marks(a);
+    // the workgroup's own tiles in the LDS form: a strided run of its XCD's
+    // contiguous range, 64 marks at a time and alike in every wave
+    const int slots = dense / kXCD, per = (tiles + kXCD - 1) / kXCD;
+    const int last = min(tiles, (b % kXCD + 1) * per);
+    int base = b % kXCD * per + b / kXCD;
+    auto own = [&](int from) {
+        const int t = from + lane * slots;
+        return t < last && ((const uint8_t *)marks)[t] != 0;
+    };
+    bool marked = own(base);
+    if (words <= kScanWords) {
+        // thread t counts the marks of words t, t + 256, ... (a word holds none
+        // past the tiles)
+        auto word = [&](int i) {
+            const uint32_t v = i < words ? marks[i] & 0x01010101u : 0u;
+            return 4 * i + 4 > tiles && i < words ? v & ((1u << (8 * (tiles & 3))) - 1u) : v;
+        };
+        uint32_t mine = 0;
+#pragma unroll
+        for (int k = 0; k < kScanWords / 256; ++k)
+            mine += (uint32_t)__popc(word((int)threadIdx.x + 256 * k));
+        uint32_t upto = mine;
+#pragma unroll
+        for (int m = 1; m < 64; m *= 2) {
+            const uint32_t v = (uint32_t)__shfl_up((int)upto, m, 64);
+            upto += lane >= m ? v : 0u;
         }
+        if (lane == 63) wave_n[wave] = upto;
         __syncthreads();
+        const uint32_t n0 = wave_n[0], n1 = wave_n[1], n2 = wave_n[2],
+                       total = n0 + n1 + n2 + wave_n[3];
+        if (total * 8u <= (uint32_t)dense) {        // few
+            if ((uint32_t)b >= total * 8u) return;  // uniform
+            const uint32_t rank = (uint32_t)b / 8u;  // of the tile this workgroup takes 32 pixels of
+            s_before[threadIdx.x] =
+                upto - mine + (wave > 0 ? n0 : 0u) + (wave > 1 ? n1 : 0u) + (wave > 2 ? n2 : 0u);
+            __syncthreads();
+            int t = 0;  // the thread that counted it
+#pragma unroll
+            for (int m = 128; m > 0; m /= 2) t += s_before[t + m] <= rank ? m : 0;
+            uint32_t left = rank - s_before[t], v = word(t);
+            int i = t;
+            for (uint32_t n; left >= (n = (uint32_t)__popc(v)); v = word(i)) left -= n, i += 256;
+            for (; left > 0u; --left) v &= v - 1u;
+            const int gxt = (a.w + kVX - 1) / kVX, tile = 4 * i + (__ffs((int)v) - 1) / 8;
+            const int px = b % 8 * kGroups + (int)threadIdx.x / 8;
+            const int x = tile % gxt * kVX + px % kVX, y = tile / gxt * kVY + px / kVX;
+            if (x < a.w && y < a.h) spatial_estimate<T, R, true>(a, x, y, (int)threadIdx.x & 7);
+            return;
+        }
     }
+    for (; base < last; base += 64 * slots, marked = own(base))
+        for (uint64_t set = __ballot(marked); set != 0ull; set &= set - 1ull) {
+            __syncthreads();  // the last tile is read
+            variance_dense_tile<T, R>(a, base + (__ffsll((unsigned long long)set) - 1) * slots,
+                                      s_g, s_m, s_d, s_px, wave_n);
+        }
 }
 
 template <typename T>
@@ -398,10 +526,8 @@ void launch_radius(const VarianceArgs &a, unsigned grid, bool listed, hipStream_
     const int tiles = ((a.w + kVX - 1) / kVX) * ((a.h + kVY - 1) / kVY);
     if (!listed && !record_pass(&point_batch_launch<T>, a, tiles)) {
         hipLaunchKernelGGL(variance_point_k<T>, dim3(grid), dim3(256), 0, s, a);
-        // (grid, one workgroup per tile, and kDenseBlocks are multiples of kXCD)
-        const int dense = (int)std::min<unsigned>(grid, kDenseBlocks);
-        hipLaunchKernelGGL((variance_short_k<T, R>), dim3(dense + kSpatialBlocks), dim3(256), 0,
-                           s, a, dense);
+        hipLaunchKernelGGL((variance_short_k<T, R>), dim3(dense_blocks<R>() + kSpatialBlocks),
+                           dim3(256), 0, s, a, dense_blocks<R>());
         return;
     }
     if (record_pass(&spatial_batch_launch<T, R>, a, 0)) return;

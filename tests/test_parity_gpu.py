@@ -374,13 +374,14 @@ def _dense_inputs(H, W, radius):
     return z, m1, m2c, short, run, oracle
 
 
+@pytest.mark.parametrize("H,W", [(37, 330), (65, 900)])
 @pytest.mark.parametrize("radius", [0, 2, 3, 7])
-def test_variance_forms_leave_empty_moments_out(radius):
+def test_variance_forms_leave_empty_moments_out(radius, H, W):
     """The window holds non-empty pixels only: moments of empty pixels that
     are not finite enter neither form, at exact counts of live short pixels
     per 64x4 tile either side of the line between the forms (65) and up to a
-    whole tile."""
-    H, W = 37, 330
+    whole tile.  (60 tiles, where dense ones take the listed form too, and 255,
+    where they take the LDS form.)"""
     z, m1, m2c, short, run, oracle = _dense_inputs(H, W, radius)
     bad = np.array([np.nan, np.inf, -np.inf], np.float32)
     where = np.flatnonzero(z == 0)
@@ -394,12 +395,12 @@ def test_variance_forms_leave_empty_moments_out(radius):
         np.testing.assert_array_equal(got, run(hn), err_msg=str(count))
 
 
+@pytest.mark.parametrize("H,W", [(37, 330), (65, 900)])
 @pytest.mark.parametrize("radius", [0, 1, 3, 6])
-def test_variance_forms_agree_on_infinite_moments(radius):
+def test_variance_forms_agree_on_infinite_moments(radius, H, W):
     """A live pixel whose second moment is infinite (binary32 overflow of
     the squared luminance) has an infinite variance in either form, and the
     forms agree where the weighted sums overflow."""
-    H, W = 37, 330
     z, m1, m2c, short, run, _ = _dense_inputs(H, W, radius)
     few, listed = short(1), short(64)
     inf = m2c.copy()
@@ -412,6 +413,57 @@ def test_variance_forms_agree_on_infinite_moments(radius):
         for count in (65, 200, 256):
             dense = run(np.where(short(count), 1, 12).astype(np.uint8), h1, h2)
             np.testing.assert_array_equal(dense[listed], got[listed], err_msg=f"{what} {count}")
+
+
+@pytest.mark.parametrize("H,W,radius,dtype", [
+    (66, 900, 3, torch.float32), (66, 900, 3, torch.float16), (66, 900, 5, torch.float32),
+    (66, 900, 6, torch.float16), (66, 900, 7, torch.float32),
+    # marks in more words than a workgroup's threads load at a time
+    (1110, 1930, 1, torch.float32)])
+def test_variance_dense_tiles_few_and_many(H, W, radius, dtype):
+    """Dense tiles beside listed ones, either side of the number (96) up to
+    which they take the listed form, at the start, the end and in between,
+    bitwise as when every pixel is short; on a workspace that an earlier use
+    left full of garbage past its counters."""
+    r = np.random.default_rng(740 + radius)
+    gxt = (W + 63) // 64
+    tile = np.arange(H)[:, None] // 4 * gxt + np.arange(W)[None, :] // 64
+    tiles = int(tile.max()) + 1
+    q = lambda a: a.astype(np.float16).astype(np.float32) if dtype == torch.float16 else a
+    z, dzdx, dzdy, n = (q(a) for a in random_gbuf(r, H, W))
+    z[r.random((H, W)) < 0.02] = 0.0
+    m1 = r.uniform(0.1, 1.0, (H, W)).astype(np.float32)
+    m2c = (m1 * m1 * r.uniform(0.0, 1.0, (H, W))).astype(np.float32)
+    g = L.GBuf(dev(z, W, dtype), dev(dzdx, W, dtype), dev(dzdy, W, dtype), dev(n, W, dtype))
+    d1, d2 = dev(m1), dev(m2c)
+    work = L.variance_workspace(empty_like_dev((H, W)))
+    words = work.view(torch.int32)
+
+    def run(hn):
+        words[256:].copy_(torch.randint(-2**31, 2**31 - 1, (words.numel() - 256,),
+                                        device="cuda", dtype=torch.int32))
+        out = empty_like_dev((H, W))
+        L.sv_variance(d1, d2, dev(hn, None, torch.uint8), g, out,
+                      L.VarianceParams(radius=radius), work)
+        assert list_consumed(work)
+        return host(out)
+
+    say(f"variance few and many dense tiles {H}x{W} radius {radius}")
+    full = run(np.ones((H, W), np.uint8))
+    if H < 1000:
+        ref = O.variance(m1, m2c.astype(np.float64) + m1.astype(np.float64) ** 2,
+                         np.ones((H, W), np.uint8), z, dzdx, dzdy, n, radius=radius)
+        assert rel_err(full, ref) <= TOL32
+    sparse = r.random((H, W)) < 0.1
+    inner = np.arange(tiles)  # a whole tile each: the last column and row of tiles are cut
+    inner = inner[(inner % gxt < W // 64) & (inner // gxt < H // 4)]
+    for count in (1, 95, 96, 97, len(inner)):
+        for pick in (inner[:count], inner[-count:], np.sort(r.permutation(inner)[:count])):
+            short = np.isin(tile, pick) | (sparse & ~np.isin(tile, inner[::7]))
+            got = run(np.where(short, 1, 12).astype(np.uint8))
+            np.testing.assert_array_equal(got[short], full[short], err_msg=str(count))
+            rest = ~short & (z > 0)
+            np.testing.assert_array_equal(got[rest], np.maximum(m2c, 0)[rest])
 
 
 def test_variance_workspace_across_sizes():
