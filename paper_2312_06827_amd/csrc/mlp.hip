@@ -30,33 +30,49 @@ __device__ __forceinline__ uint32_t plane_off(const MlpArgs &a, int p) {
 
 // A wave takes 64 pixels at a time, as two 32-pixel blocks: block hf's
 // outputs are then kept by the lanes of half hf, so that the heads, the
-// plane addresses and the stores are one pixel per lane. One head
-// evaluation per 64 pixels instead of two, and one-instruction roundings:
-// 43 -> 31 us at 1920x1080 (83 MB: 16 us at the rate of a large copy).
-__global__ __launch_bounds__(256) void mlp_forward_k(MlpArgs a) {
+// plane addresses and the stores are one pixel per lane.  One head
+// evaluation per 64 pixels instead of two, one-instruction roundings, and
+// the next group's features loaded before a group's heads (the first ones
+// beside the weights), in the 128 registers of four waves per SIMD:
+// 38 -> 24 us at 1920x1080 (83 MB: 16 us at the rate of a large copy; 28 us
+// with each group's loads at its start, 27 us at three waves per SIMD), and
+// 3.55 -> 3.65 at 64x64, where staging the weights in LDS is one step more
+// (3.8 with the loads after it).
+__global__ __launch_bounds__(256, 4) void mlp_forward_k(MlpArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 31, hf = lane >> 5;
     __shared__ u32x4 s_w[kNetStage];
     __shared__ __align__(16) float s_b[kNetFloats];
     NetStage ns;
     net_issue(a.params, a.wq, ns);
+    int g = blockIdx.x * 4 + wave;
+    const auto load = [&](bf16x8 (&x)[2]) {
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk)
+            x[blk] = load_x(a, min(min(g, a.ngrp - 1) * 64 + blk * 32 + col, a.npix - 1), hf);
+    };
+    // the first features are in flight while the weights are staged
+    bf16x8 x[2];
+    load(x);
     net_store(ns, s_w, s_b);
     __syncthreads();
     NetW f;
     load_operands(s_w, lane, f);
     load_floats(s_b, hf, f);
-    for (int g = blockIdx.x * 4 + wave; g < a.ngrp; g += gridDim.x * 4) {
+    while (g < a.ngrp) {
         const int p = g * 64 + lane;
         float o0 = 0.f, o1 = 0.f;
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) {
             FwdOut r;
-            forward_block(f, load_x(a, min(g * 64 + blk * 32 + col, a.npix - 1), hf), r);
+            forward_block(f, x[blk], r);
             if (blk == hf) {
                 o0 = r.o0;
                 o1 = r.o1;
             }
         }
+        g += gridDim.x * 4;
+        if (g < a.ngrp) load(x);
         if (p < a.npix) {
             const uint32_t o = plane_off(a, p);
             float al, ka;

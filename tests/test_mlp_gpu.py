@@ -89,6 +89,24 @@ def test_forward_parity(H, W):
     assert np.all(ek <= bk + 1e-6), np.argmax(ek - bk)
 
 
+@pytest.mark.parametrize("reps,N", [(1, 65), (3, 257), (2100, 257)])
+def test_forward_of_repeated_pixels(reps, N):
+    """A pixel set repeated, ragged against the 64-pixel groups: one group,
+    a few, and more than the resident waves (so the loop with its next
+    group's loads runs): every repetition bitwise the first, and that one
+    as the set by itself."""
+    w = _weights(60 + N)
+    xs = M.bf16(np.random.default_rng(N).normal(0, 1.2, (14, N)))
+    mlp = _device_mlp(w)
+    one = [torch.empty((1, N), device="cuda") for _ in range(2)]
+    L.sv_mlp_forward(mlp, _rows(xs), one[0], one[1], one[0])
+    out = [torch.full((reps, N), float("nan"), device="cuda") for _ in range(2)]
+    say(f"mlp forward {reps} x {N}")
+    L.sv_mlp_forward(mlp, _rows(np.tile(xs, (1, reps))), out[0], out[1], out[0])
+    for a, b in zip(out, one):
+        assert torch.equal(a, b.expand(reps, N))
+
+
 @pytest.mark.parametrize("N", [40, 1000, 4096 + 17])
 def test_backward_parity(N):
     w = _weights(20 + N)
