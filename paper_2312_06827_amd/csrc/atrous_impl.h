@@ -815,7 +815,7 @@ __device__ __forceinline__ void hv_issue(const AtrousArgs &a, int x0, int y, HvR
 
 template <int STEP>
 __device__ __forceinline__ void hv_store(const HvRow<STEP> &q, float4 *s_cl, float4 *s_gn,
-                                         float2 *s_pf) {
+                                         float *s_pf) {
     using S = HvShape<STEP>;
     const int lx = threadIdx.x;
 #pragma unroll
@@ -829,12 +829,15 @@ __device__ __forceinline__ void hv_store(const HvRow<STEP> &q, float4 *s_cl, flo
                          : make_float4(0.f, 0.f, 0.f, 0.f);
         }
     }
+    // the prefilter's entries as in the tile: -0 where there is no variance.
+    // (With a weight beside each entry, twice the LDS, step 32 took 180
+    // registers and two waves per SIMD instead of 166 and three: 53 us instead
+    // of 44 at 1920x1080 in binary32.)
 #pragma unroll
     for (int it = 0; it < S::ITP; ++it) {
         const int i = lx + it * 64;
         if (i < 3 * S::PFC)
-            s_pf[i] = (q.pin[it] != 0u && !empty_px(q.pz[it])) ? make_float2(q.pv[it], 1.f)
-                                                         : make_float2(0.f, 0.f);
+            s_pf[i] = (q.pin[it] != 0u && !empty_px(q.pz[it])) ? q.pv[it] + 0.f : -0.f;
     }
 }
 
@@ -843,7 +846,7 @@ __device__ __forceinline__ void hv_store(const HvRow<STEP> &q, float4 *s_cl, flo
 struct HvSlot {
     float4 c;   // r, g, b (rounded to the storage type), L (+inf: not a tap)
     float4 gn;  // z (0: not a tap), normal
-    float v;    // input variance (0 when not a tap)
+    float v;    // input variance (-0 when not a tap)
     float g;    // prefiltered variance
     float dzdy, kap;
 };
@@ -851,7 +854,7 @@ struct HvSlot {
 template <typename T, int STEP, int OUT, int MODE, int SLOT>
 __device__ __forceinline__ void hv_row(const AtrousArgs &ah, const AtrousArgs &av, int x0, int ph,
                                        int j0, int ro, HvSlot (&ring)[5], float4 *s_cl,
-                                       float4 *s_gn, float2 *s_pf, HvRow<STEP> &q) {
+                                       float4 *s_gn, float *s_pf, HvRow<STEP> &q) {
     using S = HvShape<STEP, OUT>;
     // packed: MODE & 1 = weights, MODE & 2 = variance, MODE & 4 = polynomial normal term
     constexpr bool WANT_VAR = (MODE & 2) != 0;
@@ -871,7 +874,7 @@ __device__ __forceinline__ void hv_row(const AtrousArgs &ah, const AtrousArgs &a
     const int ci = lx + S::HX;
     const float4 pc = s_cl[ci], pg = s_gn[ci];
     cur.gn = pg;
-    cur.v = s_pf[S::PFC + lx + 1].x;
+    cur.v = s_pf[S::PFC + lx + 1];
     cur.dzdy = dzdy;
     cur.kap = kap;
     {
@@ -880,10 +883,10 @@ __device__ __forceinline__ void hv_row(const AtrousArgs &ah, const AtrousArgs &a
         for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
             for (int dx = 0; dx < 3; ++dx) {
-                const float2 e = s_pf[dy * S::PFC + lx + dx];
-                const float kk = e.y * (kG3[dx] * kG3[dy]);
-                s = fmaf(kk, e.x, s);
-                sw += kk;
+                const float e = s_pf[dy * S::PFC + lx + dx];
+                const float kk = kG3[dx] * kG3[dy];
+                s = fmaf(kk, e, s);  // kk * -0 adds nothing
+                sw += tile_no_var(e) ? 0.f : kk;
             }
         cur.g = pf_mean(s, sw);
     }
@@ -996,7 +999,7 @@ inline int hv_tiles(const AtrousArgs &a, int rows) {
 // bit 1 = variance output, bit 2 = the normal term as a polynomial.
 template <typename T, int STEP, int OUT, int MODE>
 __device__ __forceinline__ void hv_tile(const HvArgs &a, int t, float4 *s_cl, float4 *s_gn,
-                                        float2 *s_pf) {
+                                        float *s_pf) {
     using S = HvShape<STEP, OUT>;
     const int gxt = (a.w + 63) / 64;
     const int cx = t % gxt, rest = t / gxt;
@@ -1027,12 +1030,20 @@ __device__ __forceinline__ void hv_tile(const HvArgs &a, int t, float4 *s_cl, fl
     }
 }
 
+// Waves per SIMD that the registers have to leave room for: four in the unit
+// forms of 16 rows in binary16, which take 131 or 132 registers by themselves.
 template <typename T, int STEP, int OUT, int MODE>
-__global__ __launch_bounds__(64) void atrous_hv_k(HvArgs a, int tiles) {
+constexpr int hv_waves() {
+    return sizeof(T) == 2 && STEP >= 4 && STEP <= 16 && OUT == 16 && MODE == 2 ? 4 : 1;
+}
+
+template <typename T, int STEP, int OUT, int MODE>
+__global__ __launch_bounds__(64, (hv_waves<T, STEP, OUT, MODE>())) void atrous_hv_k(HvArgs a,
+                                                                                   int tiles) {
     using S = HvShape<STEP, OUT>;
     __shared__ float4 s_cl[S::COLS];
     __shared__ float4 s_gn[S::COLS];
-    __shared__ float2 s_pf[3 * S::PFC];
+    __shared__ float s_pf[3 * S::PFC];
     const int t = xcd_tile(tiles);
     if (t < 0) return;
     hv_tile<T, STEP, OUT, MODE>(a, t, s_cl, s_gn, s_pf);
@@ -1044,7 +1055,7 @@ __global__ __launch_bounds__(64) void atrous_hv_batch_k(const HvArgs *args, cons
     using S = HvShape<STEP, OUT>;
     __shared__ float4 s_cl[S::COLS];
     __shared__ float4 s_gn[S::COLS];
-    __shared__ float2 s_pf[3 * S::PFC];
+    __shared__ float s_pf[3 * S::PFC];
     int s = 0;
     const int lt = batch_tile(prefix, n, total, s);
     if (lt < 0) return;
