@@ -272,10 +272,15 @@ struct TileShape {
     static constexpr int PFR = PF_TILE ? 0 : MID_TILE ? 2 : 3;
     static constexpr int NP = TY * PFR * PFC, ITP = (NP + NT - 1) / NT;
     // LDS bytes of one workgroup, and the waves per SIMD of the workgroups
-    // that fit a CU's 160 KiB: the register budget is set to match, so
-    // registers never hold occupancy below what LDS allows
+    // that fit a CU's 160 KiB: the register budget is set to match.  Step 1
+    // with one row per thread (small frames) fits eight, and 64 registers are
+    // too few for it: it spilled up to 20 bytes a lane (binary16 up to 64).
+    // At six waves nothing spills: 448x256 6.2 -> 5.7 us, binary16 7.3 -> 5.5
+    // (two rows: 7.2)
     static constexpr int LDS = NS * 32 + (NEED_V ? NS * 4 : 4) + (NP > 0 ? NP * 4 : 4);
-    static constexpr int FIT = 163840 / LDS * (NT / 256), WAVES = FIT < 8 ? FIT : 8;
+    static constexpr int FIT = 163840 / LDS * (NT / 256);
+    static constexpr int TOP = STEP == 1 && PY == 1 && DIR == kDir2D ? 6 : 8;
+    static constexpr int WAVES = FIT < TOP ? FIT : TOP;
 };
 
 // Raw values of one tile held in registers between issue and LDS store.

@@ -31,3 +31,13 @@ def _scratch(source):
 def test_no_scratch_memory(source):
     spilled = {k: v for k, v in _scratch(source).items() if v}
     assert not spilled
+
+
+@pytest.mark.skipif(not os.path.exists(B.HIPCC), reason="no HIP compiler")
+@pytest.mark.parametrize("source", ["atrous_f32_2d.hip", "atrous_f16_2d.hip"])
+def test_small_frame_level_has_no_scratch_memory(source):
+    """Step 1 with one row per thread, as small frames and batches run it."""
+    one_row = re.compile(r"(13atrous_tile_kI(f|DF16_)Li1ELi1E.*Lb0EEE|14atrous_batch_kI(f|DF16_)Li1ELi1E)")
+    kernels = {k: v for k, v in _scratch(source).items() if one_row.search(k)}
+    assert kernels
+    assert not {k: v for k, v in kernels.items() if v}
