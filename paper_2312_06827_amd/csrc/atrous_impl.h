@@ -437,12 +437,20 @@ __device__ __forceinline__ void tile_compute(const AtrousArgs &a, TileOrigin t,
                 s = fmaf(kG3[dx] * kG3[dy], e[i], s);
             }
             float sw = 1.f;
-            if (!(s == s) || (int32_t)sign < 0) {
+            if (S::PF_TILE) {
+                // every entry the tile's: a -0 added nothing
+                if ((int32_t)sign < 0) {
+                    sw = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 9; ++i)
+                        sw += tile_no_var(e[i]) ? 0.f : kG3[i % 3] * kG3[i / 3];
+                }
+            } else if (!(s == s) || (int32_t)sign < 0) {
                 s = sw = 0.f;
 #pragma unroll
                 for (int i = 0; i < 9; ++i) {
-                    const bool tile = S::PF_TILE || (S::MID_TILE && i / 3 == 1);
-                    const bool ok = !(tile && tile_no_var(e[i])) && (S::PF_TILE || e[i] == e[i]);
+                    const bool tile = S::MID_TILE && i / 3 == 1;
+                    const bool ok = !(tile && tile_no_var(e[i])) && e[i] == e[i];
                     const float kk = ok ? kG3[i % 3] * kG3[i / 3] : 0.f;
                     s = fmaf(kk, ok ? e[i] : 0.f, s);
                     sw += kk;
