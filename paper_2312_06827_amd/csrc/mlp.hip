@@ -536,8 +536,11 @@ __global__ __launch_bounds__(256) void kappa_grad_k(KappaGradArgs a) {
             const double ey = np_[1] - (double)nyq[j];
             const double ez = np_[2] - (double)nzq[j];
             const double cs = 1.0 - 0.5 * (ex * ex + ey * ey + ez * ez);
-            // sigma_n log(cos), 0 where the normal weight is off
-            const double ln = a.sigma_n > 0.f ? (double)a.sigma_n * log(cs > 0.0 ? cs : 0.0) : 0.0;
+            // sigma_n log(cos), 0 where the normal weight is off or 1 whatever
+            // sigma_n is (an infinite one times log(1) would be NaN)
+            const double ln = a.sigma_n > 0.f && !(cs >= 1.0)
+                                  ? (double)a.sigma_n * log(cs > 0.0 ? cs : 0.0)
+                                  : 0.0;
             const double adl = fabs(lp - luma_d(cq[0], cq[1], cq[2]));
             w = exp(ln - fabs(zp - (double)zq[j]) / den - adl * inv_dl);
             d = w * adl * dscale;

@@ -311,6 +311,25 @@ def test_alpha_grad_parity():
     assert e <= 1e-5
 
 
+def test_kappa_grad_of_infinite_sigma_n():
+    """cos^inf is 1 where two normals are the same and 0 elsewhere: on a
+    plane of one normal, the gradient without the normal weight."""
+    H, W = 9, 70
+    r = np.random.default_rng(3)
+    full = lambda v: torch.full((H, W), v, device="cuda")
+    g = L.GBuf(full(2.0), full(0.1), full(0.1), torch.stack([full(0.0), full(0.6), full(0.8)]))
+    c, y = (dev(r.uniform(0.1, 1.0, (3, H, W)).astype(np.float32)) for _ in range(2))
+    var = dev(r.uniform(0.001, 0.05, (H, W)).astype(np.float32))
+    got = []
+    for sigma_n in (np.inf, 0.0):
+        say(f"kappa grad sigma_n={sigma_n}")
+        dk = torch.zeros((H, W), device="cuda")
+        L.sv_atrous_kappa_grad(c, var, g, full(1.0), y, dk, 1, L.AtrousParams(sigma_n=sigma_n))
+        got.append(host(dk))
+    assert np.isfinite(got[1]).all() and np.abs(got[1]).max() > 0
+    np.testing.assert_array_equal(got[0], got[1])
+
+
 @pytest.mark.parametrize("step", [1, 4])
 def test_kappa_grad_parity(step):
     H, W = 48, 80
