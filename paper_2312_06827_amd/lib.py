@@ -279,8 +279,10 @@ def _lead(x: Planes) -> torch.Tensor:
 
 
 def dims_of(t: torch.Tensor) -> sv_dims:
-    p = t if t.dim() in (2, 3) else t[0]
-    return sv_dims(p.shape[-1], p.shape[-2], p.stride(-2))
+    if t.dim() == 3 and t.shape[0] > 0:  # the first plane's, without a view of it
+        return sv_dims(t.shape[2], t.shape[1], t.stride(1))
+    p = t if t.dim() == 2 else t[0]
+    return sv_dims(p.shape[1], p.shape[0], p.stride(0))
 
 
 def dtype_of(t: torch.Tensor) -> int:

@@ -195,6 +195,20 @@ def test_binding_rejects_host_tensors():
         L.sv_tonemap(t, t)
 
 
+def test_dims_of_a_tensor():
+    """A plane, or the first plane of a tensor; a tensor without one is
+    refused."""
+    import torch
+
+    dims = lambda t: (lambda d: (d.w, d.h, d.pitch))(L.dims_of(t))
+    assert dims(torch.empty(4, 6)[:, :5]) == (5, 4, 6)
+    assert dims(torch.empty(3, 4, 6)[:, :, :5]) == (5, 4, 6)
+    assert dims(torch.empty(1, 4, 5)) == (5, 4, 5)
+    for shape in ((0, 4, 5), (0,)):
+        with pytest.raises(IndexError):
+            L.dims_of(torch.empty(shape))
+
+
 def test_mlp_validation(so):
     r = ctypes.byref
     base = [A + i * 0x01000000 for i in range(48)]
