@@ -123,9 +123,10 @@ __device__ __forceinline__ float add_normal_term(float e, float s2, const Normal
 // polynomial (add_normal_poly), with no logarithm.
 constexpr float kSeriesMinSigmaN = 96.0f;
 
-// log2(1 - s2/2) / s2 on 0 <= s2 <= 0.22 to 7e-9 of itself: the polynomial of
+// log2(1 - s2/2) / s2 on 0 <= s2 <= 0.22 to 1.4e-8 of itself: the polynomial of
 // degree 4 with the smallest largest relative error there (a weighted
-// least-squares fit, reweighted until the error is level).
+// least-squares fit, reweighted until the error is level, 7e-9), its
+// coefficients kept to eight decimals, which costs the other half.
 constexpr double kNormalPoly[5] = {-0.72134753, -0.18033577, -0.06015212, -0.02204816,
                                    -0.01145215};
 
@@ -137,16 +138,16 @@ inline NormalCoef make_normal_coef(float sigma_n) {
 }
 
 // The same term for large sigma_n without the logarithm: sigma_n s2 Q(s2) by
-// Horner, sigma_n in the coefficients.  The polynomial's 7e-9 is below
-// binary32's own rounding for every weight above 1e-6 of the centre's at
-// sigma_n = 128 (s2 = 0.216 there; at 96, above 2.6e-5).  The Taylor sum
-// through (s2/2)^6 / 6, one term more, leaves 4e-6 at 1e-6.  Where s2 is
+// Horner, sigma_n in the coefficients.  The polynomial's 1.4e-8 is below
+// binary32's own rounding (3e-8) up to s2 = 0.22, that is for every weight
+// above 3.3e-7 of the centre's at sigma_n = 128 and above 1.4e-5 at 96: 2e-7
+// of the smallest such weight.  The Taylor sum through (s2/2)^6 / 6, one term
+// more, leaves 4e-6 of it.  Where s2 is
 // larger the polynomial gives an exponentially small weight, as the exact one
 // is (or zero: every coefficient is negative), so no clamp is needed; and no
 // 1 - s2/2 is rounded, so no residual term either.  Five instructions where
 // the sum and its scaling took seven: the five 5x5 levels of a 1080p frame
-// 253 -> 245 us (with sigma_n apart and literal coefficients 248, with the
-// coefficients held in vector registers 247).
+// 253 -> 247 us (with sigma_n apart and literal coefficients 248).
 __device__ __forceinline__ float add_normal_poly(float e, float s2, const NormalCoef &k) {
     float p = fmaf(k.q[4], s2, k.q[3]);
     p = fmaf(p, s2, k.q[2]);
