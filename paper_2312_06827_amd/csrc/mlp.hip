@@ -460,12 +460,11 @@ __device__ __forceinline__ double px_sum(double v) {
 // Four lanes per pixel, taps read directly, in binary64 (see alpha_grad_k):
 // lane s takes window taps s, s + 4, ... with every load issued before the
 // first use.  The training frames are small, so one thread per pixel left the
-// chip at one wave per SIMD walking 25 taps one after the other: 32 us per level at 320x180
-// against 20 (eight lanes: 23, its sums across lanes cost more).  The
-// tap's three weights are one exponential of the summed exponents.
+// chip at one wave per SIMD walking 25 taps one after the other: 32 us per
+// level at 320x180 against 20 (eight lanes: 23, its sums across lanes cost
+// more).  The tap's three weights are one exponential of the summed exponents.
 // The 3x3 variance prefilter runs over the in-image, non-empty taps, as in
 // the level itself.
-
 template <typename T>
 __global__ __launch_bounds__(256) void kappa_grad_k(KappaGradArgs a) {
     constexpr int L = kKappaLanes, NT = (25 + L - 1) / L, NV = (9 + L - 1) / L;
@@ -579,6 +578,10 @@ __global__ __launch_bounds__(256) void kappa_grad_k(KappaGradArgs a) {
 // per wave as it takes.  The backward pass keeps its weights and its
 // sums in registers, two waves per SIMD; more workgroups than are
 // resident would only repeat its loads of the weights and its final sums.
+// It walks blocks of 32 pixels, so a wave has two of them at least.  With one
+// (twice the workgroups) the smallest frames gain, 64x64 13.9 -> 12.4 us and
+// 480x270 21.3 -> 19.2, but at 256x256 and the trainer's 320x180 the doubled
+// sums cost more: 15.9 -> 16.9 and 15.7 -> 17.8.
 constexpr int kFwdPerCU = 8, kBwdPerCU = 2;
 
 inline unsigned mlp_grid(int ngrp, int per_cu) {
@@ -612,7 +615,8 @@ extern "C" int sv_mlp_forward(const sv_mlp *w, const void *feat, float *alpha, f
     a.pitch = d.pitch;
     a.npix = d.w * d.h;
     a.ngrp = (a.npix + 63) / 64;
-    hipLaunchKernelGGL(mlp_forward_k, dim3(mlp_grid(a.ngrp, kFwdPerCU)), dim3(256), 0, as_stream(stream), a);
+    hipLaunchKernelGGL(mlp_forward_k, dim3(mlp_grid(a.ngrp, kFwdPerCU)), dim3(256), 0,
+                       as_stream(stream), a);
     return hip_status(hipGetLastError());
 }
 
@@ -653,8 +657,10 @@ extern "C" int sv_mlp_backward(const sv_mlp *w, const void *feat, const float *d
     const span gs{(uintptr_t)grad, (uintptr_t)grad + SV_MLP_PARAMS * sizeof(float)};
     const span fs{(uintptr_t)feat, (uintptr_t)feat + (size_t)d.w * (size_t)d.h * 32u};
     if (overlaps(ws, gs) || overlaps(ws, fs) || overlaps(gs, fs) ||
-        (d_alpha && (overlaps(ws, plane_span(d_alpha, d, 4)) || overlaps(gs, plane_span(d_alpha, d, 4)))) ||
-        (d_kappa && (overlaps(ws, plane_span(d_kappa, d, 4)) || overlaps(gs, plane_span(d_kappa, d, 4)))))
+        (d_alpha &&
+         (overlaps(ws, plane_span(d_alpha, d, 4)) || overlaps(gs, plane_span(d_alpha, d, 4)))) ||
+        (d_kappa &&
+         (overlaps(ws, plane_span(d_kappa, d, 4)) || overlaps(gs, plane_span(d_kappa, d, 4)))))
         return SV_EALIAS;
     const unsigned grid = mlp_grid(a.ngrp, kBwdPerCU);
     hipStream_t s = as_stream(stream);

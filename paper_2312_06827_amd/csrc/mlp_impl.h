@@ -10,7 +10,7 @@
 // A's and B's agree.  The result D[8 (r/4) + 4 (l/32) + r % 4][l % 32] is in
 // accumulator r = 0..15, so after a layer, accumulators 8 j .. 8 j + 7 of a
 // lane, rounded in pairs, are that lane's operand j of the next layer:
-// activations never leave registers in the forward pass. 
+// activations never leave registers in the forward pass.
 //
 // Which instruction: both round a 32-term sum alike (1.07e-8 rms of the
 // summed magnitudes), but not to the same bits, and a pre-activation that
@@ -63,7 +63,6 @@ __device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c) {
 }
 
 // The same product as two K blocks of eight, in order.
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x16 mfma8(bf16x8 a, bf16x8 b, f32x16 c) {
     typedef short s16x8 __attribute__((ext_vector_type(8)));
     const s16x8 p = __builtin_bit_cast(s16x8, a), q = __builtin_bit_cast(s16x8, b);
@@ -106,14 +105,6 @@ struct NetW {
     float b3a, b3b;
 };
 
-__device__ __forceinline__ bf16x8 op_load(const uint16_t *wq, int k, int lane) {
-    u32x4 p;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        p[i] = op_element(wq, k, lane, 2 * i) | ((uint32_t)op_element(wq, k, lane, 2 * i + 1) << 16);
-    return as_operand(p);
-}
-
 // The feature operand of one lane: features 4 hf .. 4 hf + 3 and 8 + 4 hf ..
 // of a 32-byte feature row.
 __device__ __forceinline__ bf16x8 feature_operand(const uint2 *row, int hf) {
@@ -122,7 +113,8 @@ __device__ __forceinline__ bf16x8 feature_operand(const uint2 *row, int hf) {
 }
 
 // Forward pass of one 32-pixel block.  x: this lane's operand of layer 1;
-// returns the pre-activations (with biases), the activations as operands, and the two outputs of pixel lane % 32 (the same in both halves).
+// returns the pre-activations (with biases), the activations as operands, and
+// the two outputs of pixel lane % 32 (the same in both halves).
 struct FwdOut {
     f32x16 a1, a2;
     bf16x8 h1[2], h2[2];
