@@ -211,8 +211,8 @@ typedef struct {
  * am L(c), m2c = (1-am) (m2c_hist + am (L(c) - m1_hist)^2), which is the
  * central form of the EMA (1-am) E[L^2] + am L^2; the reprojected m2c is
  * the bilinear mixture's central moment (taps' m2c plus the spread of
- * their m1).  A discarded history gives out = c, m1 = L, m2c = 0, n = 1.  alpha_map, if given, replaces alpha
- * per pixel.  Outputs must not overlap any input (SV_EALIAS).  Required:
+ * their m1).  A discarded history gives out = c, m1 = L, m2c = 0, n = 1.
+ * alpha_map, if given, replaces alpha per pixel.  Outputs must not overlap any input (SV_EALIAS).  Required:
  * cur, g.z, g.n*, mvx, mvy, prev.z, prev.n*, hist, hist_m1, hist_m2c,
  * hist_n, out, out_m1, out_m2c, out_n; ids when SV_T_USE_ID. */
 int sv_temporal(const sv_temporal_io *io, sv_dims d, sv_dtype t,
@@ -236,7 +236,10 @@ typedef struct {
 /* Two passes: every pixel with n >= min_hist gets the temporal estimate and
  * the others are listed in `work`; a second pass spreads the listed pixels
  * over the whole GPU for the spatial estimate (they are few, about 1% in
- * steady motion, but clustered at disocclusions).
+ * steady motion, but clustered at disocclusions).  Where a quarter of a 64x4
+ * tile or more is short (a camera cut, a stream's first frame) the tile is
+ * marked at the end of `work` instead of listed, and computed from LDS as a
+ * whole, with the same result.  Under SV_V_LISTED everything is listed.
  * var = max(0, m2c) where n >= min_hist (m2c = E[L^2] - E[L]^2 as
  * sv_temporal writes it).  Where 1 <= n < min_hist the moments are averaged
  * over the (2 radius + 1)^2 window (inside the image, not empty) with
@@ -299,13 +302,16 @@ typedef struct {
     /* Launch shape of the LDS-tiled kernels (results do not depend on it):
      * persistent: -1 library default (one tile per workgroup), 0 one tile
      * per workgroup, 1 each
-     * workgroup loops over tiles and prefetches the next one;
+     * workgroup loops over tiles and prefetches the next one (no effect at
+     * step 32 and on adaptive levels, which run one tile per workgroup);
      * blocks_per_cu: workgroups per CU of a persistent launch (0 default);
      * tile_rows: the LDS tile's height.  5x5 levels: lattice rows per
      * thread, 1 or 2 (a tile of 64 x 4 tile_rows lattice rows); fused
      * separable levels: output rows per wave, 6 or 16.  0 = library default
-     * (5x5: 2 up to step 4, 1 above; separable: 16 up to step 4, 6 above);
-     * other values are SV_EINVAL. */
+     * (5x5: 2 up to step 4, or 1 where the two-row tiles of the frame would
+     * be no more than 256 at step 1 or 384 at steps 2 and 4, and 1 above
+     * step 4; separable: 16 up to step 4, 6 above); other values are
+     * SV_EINVAL. */
     int32_t persistent;
     int32_t blocks_per_cu;
     int32_t tile_rows;
