@@ -276,7 +276,9 @@ struct TileShape {
     // with one row per thread (small frames) fits eight, and 64 registers are
     // too few for it: it spilled up to 20 bytes a lane (binary16 up to 64).
     // At six waves nothing spills: 448x256 6.2 -> 5.7 us, binary16 7.3 -> 5.5
-    // (two rows: 7.2)
+    // (two rows: 7.2).  The adaptive step 2 spills 8 bytes at its six waves,
+    // and the persistent forms, which hold the next tile's values as well,
+    // spill at any of these
     static constexpr int LDS = NS * 32 + (NEED_V ? NS * 4 : 4) + (NP > 0 ? NP * 4 : 4);
     static constexpr int FIT = 163840 / LDS * (NT / 256);
     static constexpr int TOP = STEP == 1 && PY == 1 && DIR == kDir2D ? 6 : 8;
@@ -515,8 +517,9 @@ __device__ __forceinline__ void tile_compute(const AtrousArgs &a, TileOrigin t,
 }
 
 template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR, int NT, bool PERSIST>
-__global__ __launch_bounds__(NT) __attribute__((
-    amdgpu_waves_per_eu(TileShape<STEP, PY, DIR, WANT_VAR, NT>::WAVES))) void atrous_tile_k(AtrousArgs a, int tiles, int per_xcd) {
+__global__ __launch_bounds__(NT)
+__attribute__((amdgpu_waves_per_eu(TileShape<STEP, PY, DIR, WANT_VAR, NT>::WAVES)))
+void atrous_tile_k(AtrousArgs a, int tiles, int per_xcd) {
     using S = TileShape<STEP, PY, DIR, WANT_VAR, NT>;
     __shared__ float4 s_cl[S::NS];  // r, g, b, L (L = +inf: no tap)
     __shared__ float4 s_gn[S::NS];  // z, nx, ny, nz (z = 0: no tap)
@@ -551,8 +554,8 @@ __global__ __launch_bounds__(NT) __attribute__((
     for (;;) {
         const int tn = t + nslot;
         if (tn < last) tile_issue<T, S>(a, tile_origin<STEP, S::TY, S::TX>(tn, gxt), regs);
-        tile_compute<T, STEP, PY, MODE, WANT_VAR, DIR, NT>(a, tile_origin<STEP, S::TY, S::TX>(t, gxt),
-                                                       s_cl, s_gn, s_v, s_pf);
+        tile_compute<T, STEP, PY, MODE, WANT_VAR, DIR, NT>(
+            a, tile_origin<STEP, S::TY, S::TX>(t, gxt), s_cl, s_gn, s_v, s_pf);
         if (tn >= last) break;
         __syncthreads();
         tile_store<S>(regs, s_cl, s_gn, s_v, s_pf);
@@ -564,9 +567,9 @@ __global__ __launch_bounds__(NT) __attribute__((
 // Batched form: the tiles of many streams (each its own AtrousArgs), one
 // tile per workgroup; every tile is staged and computed exactly as above.
 template <typename T, int STEP, int PY, int MODE, bool WANT_VAR, int DIR, int NT>
-__global__ __launch_bounds__(NT) __attribute__((
-    amdgpu_waves_per_eu(TileShape<STEP, PY, DIR, WANT_VAR, NT>::WAVES))) void atrous_batch_k(const AtrousArgs *args, const int *prefix,
-                                                      int n, int total) {
+__global__ __launch_bounds__(NT)
+__attribute__((amdgpu_waves_per_eu(TileShape<STEP, PY, DIR, WANT_VAR, NT>::WAVES)))
+void atrous_batch_k(const AtrousArgs *args, const int *prefix, int n, int total) {
     using S = TileShape<STEP, PY, DIR, WANT_VAR, NT>;
     __shared__ float4 s_cl[S::NS];
     __shared__ float4 s_gn[S::NS];
@@ -1160,12 +1163,14 @@ void launch_tile_py(const AtrousArgs &a, TileCfg cfg, hipStream_t s) {
 // Two lattice rows per thread pay only while their tiles fill the chip: a
 // frame of no more of them than CUs (at steps 2 and 4, whose tiles cost more
 // to stage, than one and a half times the CUs) takes one row per thread and
-// twice the workgroups.  Per level, one row against two, at 256x256 (128
-// tiles of two rows): 6.1 against 6.6 us (step 1), 6.0 against 7.3, 6.1
-// against 7.3 (step 4); at 480x270 (272): 8.5 against 7.9, 8.4 against 8.6,
-// 7.6 against 8.7; at 640x360 (450): 10.7 against 8.5, 9.8 against 9.2, 9.5
-// against 9.4.  (A batch plan runs all its streams' tiles as one list, by one
-// kernel, so it keeps the full-size choice.)
+// twice the workgroups.  Per level, one row against two, us by the number of
+// two-row tiles: step 1 5.3 against 7.0 (128 tiles), 5.7 / 7.1 (224); step 2
+// 7.8 / 8.8 (272), 8.1 / 8.9 (360); step 4 7.1 / 8.8 (288).  The line is on
+// the safe side: above it one row still wins until the chip is full twice or
+// more, step 1 6.7 / 8.2 (272), 7.8 / 8.4 (450), 13.1 / 13.3 (1020), step 2
+// 8.8 / 9.1 (460), 10.4 / 10.9 (624), 12.1 / 11.2 (754), step 4 8.4 / 9.2
+// (480), 11.2 / 13.0 (780).  (A batch plan runs all its streams' tiles as one
+// list, by one kernel, so it keeps the full-size choice.)
 template <int STEP>
 bool few_tiles(const AtrousArgs &a) {
     if (recorder()) return false;

@@ -67,9 +67,9 @@ __device__ __forceinline__ float spatial_weight(const VarianceArgs &a, float dz,
 // ---- dense tiles ---------------------------------------------------------------
 //
 // A tile with at least kDenseTile short pixels is not listed but marked.  Many
-// of them are computed by one workgroup each:
-// its window, (64 + 2 R) x (4 + 2 R) pixels of depth, normal and moments, is
-// staged once in LDS, and the short pixels are packed onto the threads.  Every
+// of them are computed by one workgroup each: its window, (64 + 2 R) x
+// (4 + 2 R) pixels of depth, normal and moments, is staged once in LDS, and
+// the short pixels are packed onto the threads.  Every
 // value is then loaded about 2.7 times (R = 3) where the listed form gathers
 // it 49 times.  The sums run in the listed form's order (eight partial sums of
 // taps sub, sub + 8, ..., joined as its butterfly joins them), so a pixel's
@@ -78,9 +78,9 @@ __device__ __forceinline__ float spatial_weight(const VarianceArgs &a, float dz,
 // A quarter of a tile: below it the list is as fast, and its pixels spread over
 // the whole chip.  In a frame of up to kScanWords words of marks (2048 tiles),
 // up to 96 dense tiles (R <= 4, see dense_blocks) take the listed form as well,
-// straight from the marks: a workgroup per tile leaves most of the chip idle there, while in a
-// larger frame the list hides it and counting the marks (2 to 3 us at 8160
-// tiles) is the loss.
+// straight from the marks: a workgroup per tile leaves most of the chip idle
+// there, while in a larger frame the list hides it and counting the marks (2
+// to 3 us at 8160 tiles) is the loss.
 // The call with its short pixels in 16x16 patches, binary32, R = 3, everything
 // listed -> as here: at 1920x1080 none short 8.5 -> 9.5 us, 2 % 24.8 -> 24.9,
 // 20 % 128 -> 94, all 454 -> 151 (there the pointwise pass goes from 79 to 7 us:
